@@ -25,6 +25,7 @@ struct BlockShape {
     int nmax2;   // largest target order in the bin
     int BT;      // threads per workgroup: kBlockThreads or kBlockThreadsWide
     int directed = 0;   // directed database: W covers an out-row and an in-row
+    int K = 0;          // beam width
 };
 
 // Slot stride of the workgroup kernel for beam width K and `threads` per
@@ -41,6 +42,14 @@ hipError_t block_max_resident(const BlockShape &s, int *blocks_per_cu);
 hipError_t launch_block(const BlockShape &s, const DbView &src, const DbView &dst, const WorkItem *work, int nwork,
                         int *queue, Costs c, int K, int last_complete, void *workspace, size_t ws_stride,
                         Outputs out, int grid, hipStream_t stream);
+// The matrix-core form of the workgroup kernel (kb_mat.h), which the block_*
+// functions use wherever it has an instantiation for the shape.
+bool mat_supported(const BlockShape &s);
+size_t mat_workspace_bytes(const BlockShape &s);
+hipError_t mat_max_resident(const BlockShape &s, int *blocks_per_cu);
+hipError_t launch_mat(const BlockShape &s, const DbView &src, const DbView &dst, const WorkItem *work, int nwork,
+                      int *queue, Costs c, int last_complete, void *workspace, size_t ws_stride, Outputs out, int grid,
+                      hipStream_t stream);
 hipError_t launch_fill_zero(int *p, int count, hipStream_t stream);
 
 // Bipartite K-best-assignment bound, a workgroup of nwav (1 or 4) waves per

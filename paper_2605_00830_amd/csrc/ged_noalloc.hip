@@ -132,7 +132,7 @@ extern "C" ged_status ged_kbest_noalloc(ged_db *db, const ged_pair *h_pairs, int
         if (count[b] == 0) continue;
         const int threads = count[b] < 2 * (int64_t)cus ? gedk::kBlockThreadsWide : gedk::kBlockThreads;
         shape[b] = gedk::BlockShape{gedk::bin_words(b), PL, gedk::block_slot_stride(K, threads), nmax1[b], nmax2[b],
-                                    threads, directed};
+                                    threads, directed, K};
         stride[b] = gedk::block_workspace_bytes(shape[b]);
         reserve += (stride[b] + 255) & ~(size_t)255;
     }

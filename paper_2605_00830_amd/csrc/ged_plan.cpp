@@ -487,6 +487,7 @@ ged_status ged_plan_create_ex(ged_db *db, const ged_pair *h_pairs, int64_t npair
         b.shape.W = W;
         b.shape.PL = PL;
         b.shape.directed = db->directed ? 1 : 0;
+        b.shape.K = K;
         b.shape.nmax1 = std::max(b.shape.nmax1, g1.n);
         b.shape.nmax2 = std::max(b.shape.nmax2, g2.n);
         WorkItem wi;

@@ -185,6 +185,7 @@ gedk::BlockShape shape_for(const ged_server *s, int W, int nmax1, int nmax2, int
     sh.nmax1 = nmax1;
     sh.nmax2 = nmax2;
     sh.directed = s->directed ? 1 : 0;
+    sh.K = s->cfg.K;
     return sh;
 }
 

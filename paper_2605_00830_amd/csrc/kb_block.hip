@@ -1,5 +1,7 @@
 // kb_block.hip -- workgroup-per-pair K-Best search for gfx950 (any shape up
-// to 512 vertices and K = 1024).
+// to 512 vertices and K = 1024): the block_* entry points, and the kernel for
+// the shapes without a matrix-core instantiation (kb_mat.h: more than four
+// edge-label codes, the largest K, state beyond its LDS).
 //
 // One 256-thread workgroup searches one pair at a time: first the pair at
 // its own index, then further pairs from a work queue (persistent launch).
@@ -818,13 +820,16 @@ const void *select_kernel(int W, int PL, bool CL, int BT, bool DIR) {
 #define GEDK_CASE(w, pl, cl, bt, d) \
     if (W == w && PL == pl && CL == cl && BT == bt && DIR == d) return kernel_ptr<w, pl, cl, bt, d>();
 #define GEDK_ROW(w, cl, bt, d) GEDK_CASE(w, 0, cl, bt, d) GEDK_CASE(w, 2, cl, bt, d) GEDK_CASE(w, 4, cl, bt, d)
+    // (candidate matrix in LDS: without the shapes that only the matrix-core
+    // kernel's range of K could fit there)
 #define GEDK_ALL(bt)                                                                                        \
-    GEDK_ROW(1, true, bt, false) GEDK_ROW(2, true, bt, false) GEDK_ROW(4, true, bt, false)                  \
-    GEDK_ROW(8, true, bt, false) GEDK_ROW(16, true, bt, false) GEDK_ROW(1, false, bt, false)                \
-    GEDK_ROW(2, false, bt, false) GEDK_ROW(4, false, bt, false) GEDK_ROW(8, false, bt, false)               \
-    GEDK_ROW(16, false, bt, false) GEDK_ROW(2, true, bt, true) GEDK_ROW(4, true, bt, true)                   \
-    GEDK_ROW(8, true, bt, true) GEDK_ROW(16, true, bt, true) GEDK_ROW(2, false, bt, true)                   \
-    GEDK_ROW(4, false, bt, true) GEDK_ROW(8, false, bt, true) GEDK_ROW(16, false, bt, true)
+    GEDK_ROW(1, true, bt, false) GEDK_ROW(2, true, bt, false) GEDK_CASE(4, 4, true, bt, false)               \
+    GEDK_CASE(8, 4, true, bt, false) GEDK_CASE(16, 2, true, bt, false) GEDK_CASE(16, 4, true, bt, false)     \
+    GEDK_ROW(1, false, bt, false) GEDK_ROW(2, false, bt, false) GEDK_ROW(4, false, bt, false)                \
+    GEDK_ROW(8, false, bt, false) GEDK_ROW(16, false, bt, false) GEDK_ROW(2, true, bt, true)                 \
+    GEDK_ROW(4, true, bt, true) GEDK_CASE(8, 4, true, bt, true) GEDK_CASE(16, 2, true, bt, true)             \
+    GEDK_CASE(16, 4, true, bt, true) GEDK_ROW(2, false, bt, true) GEDK_ROW(4, false, bt, true)               \
+    GEDK_ROW(8, false, bt, true) GEDK_ROW(16, false, bt, true)
     GEDK_ALL(256)
     GEDK_ALL(512)
     // four waves per SIMD on one pair: the largest rows without label planes
@@ -844,13 +849,16 @@ int block_slot_stride(int K, int threads) {
     return (K + threads - 1) / threads * threads;
 }
 
-size_t block_workspace_bytes(const BlockShape &s) { return layout_for(s).stride; }
+size_t block_workspace_bytes(const BlockShape &s) {
+    return mat_supported(s) ? mat_workspace_bytes(s) : layout_for(s).stride;
+}
 
 bool block_shape_supported(const BlockShape &s) {
-    return select_kernel(s.W, s.PL, cand_in_lds(s), s.BT, s.directed != 0) != nullptr;
+    return mat_supported(s) || select_kernel(s.W, s.PL, cand_in_lds(s), s.BT, s.directed != 0) != nullptr;
 }
 
 hipError_t block_max_resident(const BlockShape &s, int *blocks_per_cu) {
+    if (mat_supported(s)) return mat_max_resident(s, blocks_per_cu);
     const void *k = select_kernel(s.W, s.PL, cand_in_lds(s), s.BT, s.directed != 0);
     if (!k) return hipErrorInvalidValue;
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k, s.BT, dyn_lds_bytes(s));
@@ -859,6 +867,9 @@ hipError_t block_max_resident(const BlockShape &s, int *blocks_per_cu) {
 hipError_t launch_block(const BlockShape &s, const DbView &src, const DbView &dst, const WorkItem *work, int nwork,
                         int *queue, Costs c, int K, int last_complete, void *workspace, size_t ws_stride,
                         Outputs out, int grid, hipStream_t stream) {
+    if (K != s.K) return hipErrorInvalidValue;
+    if (mat_supported(s))
+        return launch_mat(s, src, dst, work, nwork, queue, c, last_complete, workspace, ws_stride, out, grid, stream);
     const void *k = select_kernel(s.W, s.PL, cand_in_lds(s), s.BT, s.directed != 0);
     if (!k || grid <= 0 || s.KS != block_slot_stride(K, s.BT)) return hipErrorInvalidValue;
     BlockArgs a;

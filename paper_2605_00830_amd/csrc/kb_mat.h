@@ -1,0 +1,935 @@
+// kb_mat.h -- workgroup-per-pair K-Best search with the children scored on
+// the matrix cores: targets of up to 512 vertices (directed: 256), up to four
+// edge-label codes, K as far as mat_config() has an instantiation.
+//
+// A level's children are two contractions over g2's vertices v,
+//   kept[s][u]  = sum_v Phi_s[v] A2[u][v]     |Phi & N2(u)|
+//   inimg[s][u] = sum_v Img_s[v] A2[u][v]     |Img & N2(u)|
+// (and, with edge labels, one per label code c: Phi_c against the rows of
+// code c), which the PED of child (s, u) takes linearly:
+//   PED_s + lc(u) + edel (deg - kept) + eins (inimg - kept) + esub (kept - same).
+// The 0/1 operands are fp4 (E2M1) matrices of the 16x16x128 MFMA: 32 bits of a
+// set become four registers of nibbles by (w >> j) & 0x11111111 (value 0.5,
+// lifted to 1 by the block scale), the same permutation of v on both sides.
+// FAST: eins, -edel (+ esub) and -esub are small multiples of one integer g
+// (fp4 holds 0, 1, 2, 3, 4, 6, 8, 12 times 0.5), so they ride in the slot
+// operand and one chain gives the whole child but for its base; otherwise the
+// counts come out separately and the PED is formed in int32.  All sums are
+// whole numbers below 2^24: the f32 accumulators are exact.  Used vertices are
+// struck out by one more MFMA, a unit matrix times Img at scale 2^24.
+//
+// A wave holds NT tiles of 16 slots (their operands in registers) and walks
+// the tiles of 16 target vertices; each child is kept as one byte
+// x = clamp((PED - b) >> sh, 0, 127) in registers, four per word, so no
+// candidate matrix exists.  b is the least parent PED plus the previous
+// level's T - m0, less 63, and sh = 0: T - m0 moves by about 4 to 12 from level
+// to level on the random graphs measured (at most 46 on 200- to 500-vertex
+// pairs), so the K-th child almost always falls inside the bytes' exact range;
+// if not, coarse passes from the least parent PED (a bound of every child)
+// narrow it 6 bits at a time until it is exact.
+//
+// The threshold is searched on the bytes (SWAR compare and popcount, two
+// thresholds per round, steered by the least child plus the last level's
+// T - least child).  Survivors are marked in per-slot bit masks over u in LDS
+// and emitted slot by slot in ascending u with the tie quota counted from the
+// first slot: generation order, as in every other kernel.  Their PEDs are
+// recomputed in int32 from the sets, so the bytes only select.
+//
+// The mapping is not copied level by level.  Images of the last (incomplete)
+// block of 8 levels are per-slot rows in LDS; a complete block's rows go to
+// the workspace once, indexed by the slots of its last level, and each slot
+// carries one ancestor index per block (gathered from its parent's).  A block
+// whose ancestors have all become one slot is the same for the whole beam: it
+// leaves the window for the common mapping, whose part of Phi is built once
+// per level instead of once per slot.  (Measured window: 35 to 85 levels on
+// 200- to 450-vertex pairs at K = 256, against half of n1 for a full copy.)
+#pragma once
+
+#include "ged_internal.h"
+#include "wave_common.h"
+
+namespace gedk {
+namespace mat {
+
+using namespace wv;
+
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+constexpr uint32_t NIB = 0x11111111u;
+constexpr uint32_t HI = 0x80808080u;
+constexpr uint32_t DEAD = 0x7f7f7f7fu;      // four children that never survive
+constexpr uint32_t DEL16 = 0xffffu;
+constexpr int XCAP = 127;                   // byte of a child above the range
+constexpr int DELU = 1023;                  // survivor record's vertex of the deletion child
+constexpr int BL = 8;                       // levels per mapping block
+constexpr int SC_ONE = 128;                 // E8M0 scale 2: a 0.5 becomes 1
+constexpr int SC_BIG = 127 + 25;            // a 0.5 becomes 2^24
+constexpr float FBIG = 16777216.f;
+constexpr int64_t kFastBound = (int64_t)1 << 22;   // PEDs below this stay exact in f32 with 1 / 2^sh parts
+
+struct MatLds {
+    int rows, lc, img, phi, le, lt, anc, cur, com, nbr, nbc, pc, ped, nsub, sel, bytes;
+};
+
+struct MatArgs {
+    DbView src, dst;
+    const WorkItem *work;
+    int nwork;
+    int *queue;
+    Costs c;
+    int K;
+    int last_complete;
+    char *ws;
+    size_t ws_stride;
+    MatLds L;
+    Outputs out;
+    uint32_t pedbound;   // no PED of the launch exceeds it
+    // FAST: fp4 codes of the slot operand (Img \ Phi, Phi, Phi_c) and their unit
+    int code_img, code_phi, code_same;
+    float unit;
+};
+
+// One chain step; the operands' scales are E8M0 bytes.
+__device__ __forceinline__ v4f mfma_fp4(const uint32_t (&a)[4], const uint32_t (&b)[4], v4f c, int sa) {
+    v8i x = {}, y = {};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        x[j] = (int)a[j];
+        y[j] = (int)b[j];
+    }
+    return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(x, y, c, 4, 4, 0, sa, 0, SC_ONE);
+}
+
+__device__ __forceinline__ void spread(uint32_t w, uint32_t (&e)[4]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) e[j] = (w >> j) & NIB;
+}
+
+__device__ __forceinline__ uint32_t below(int i, int kw) {
+    const int rem = i - kw * 32;
+    return rem >= 32 ? 0xffffffffu : (rem <= 0 ? 0u : ((1u << rem) - 1u));
+}
+
+__device__ __forceinline__ unsigned long long wave_min64(unsigned long long v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const unsigned long long w = (unsigned long long)__shfl_xor((long long)v, o);
+        v = w < v ? w : v;
+    }
+    return v;
+}
+
+// W: words of a row (directed: out-half, then in-half); a wave holds NT tiles
+// of 16 slots; SW waves split the slots, UW the target tiles.
+template <int W, int NT, int SW, int UW, bool LAB, bool DIR, bool FAST, int MINW = 2>
+__global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
+    constexpr int KS = 16 * NT * SW;            // slots
+    constexpr int T = 64 * SW * UW;
+    constexpr int NWV = SW * UW;
+    constexpr int PARTS = T / KS;               // threads per slot in the update
+    constexpr int KST = W / 4;                  // 128-vertex steps of a contraction
+    constexpr int WU = DIR ? W / 2 : W;         // words that name target vertices
+    constexpr int NTL = 2 * WU / UW;            // target tiles of a wave
+    constexpr int KP = KS % 64 == 0 ? KS + 16 : (KS == 32 ? 48 : KS);   // slot stride: the four k-groups on different banks
+    constexpr int NA = LAB ? 3 : 1;             // sets: Phi / rows, and two label planes
+    constexpr int NS = LAB ? 5 : (FAST ? 1 : 2);   // slot operands (FAST: combined first; else Phi, Img first)
+    constexpr int NOP = LAB ? (FAST ? 5 : 6) : NS; // ... with four label codes after them
+    constexpr int NCAND = NTL + 1;              // words of a slot tile: target tiles, then the deletion
+    constexpr int NWP = (W + PARTS - 1) / PARTS;
+    constexpr int MAXA = 16;                    // ancestor rows a thread moves per step
+    static_assert(W % 4 == 0 && KS <= T && 8 % UW == 0 && (2 * WU) % UW == 0, "shape");
+
+    extern __shared__ uint32_t s_dyn[];
+    __shared__ uint32_t s_red[2][NWV];
+    __shared__ unsigned long long s_red64[NWV];
+    __shared__ int s_item, s_neq, s_nw;
+    __shared__ int s_sumV[2];
+    __shared__ uint32_t s_min[2];
+    char *lds = reinterpret_cast<char *>(s_dyn);
+    uint32_t *s_rows = reinterpret_cast<uint32_t *>(lds + a.L.rows);   // [NA][W][urs]
+    float *s_lc = reinterpret_cast<float *>(lds + a.L.lc);             // label cost of u (FAST: float, else int bits)
+    int *s_lci = reinterpret_cast<int *>(lds + a.L.lc);
+    uint32_t *s_img = reinterpret_cast<uint32_t *>(lds + a.L.img);     // [W][KP]; bits >= n2 set: never free
+    uint32_t *s_phi = reinterpret_cast<uint32_t *>(lds + a.L.phi);     // [NA][W][KP] the window's part of Phi
+    uint32_t *s_le = reinterpret_cast<uint32_t *>(lds + a.L.le);       // [WU + 1][KP] children at most T (last: deletion)
+    uint32_t *s_lt = reinterpret_cast<uint32_t *>(lds + a.L.lt);       // ... below T
+    uint16_t *s_anc = reinterpret_cast<uint16_t *>(lds + a.L.anc);     // [blocks][KS]
+    uint16_t *s_cur = reinterpret_cast<uint16_t *>(lds + a.L.cur);     // [BL][KS]
+    uint16_t *s_com = reinterpret_cast<uint16_t *>(lds + a.L.com);     // common mapping
+    uint16_t *s_nbr = reinterpret_cast<uint16_t *>(lds + a.L.nbr);     // window neighbours of v_i (bit 15: in-arc)
+    uint8_t *s_nbc = reinterpret_cast<uint8_t *>(lds + a.L.nbc);       // their label codes
+    uint32_t *s_pc = reinterpret_cast<uint32_t *>(lds + a.L.pc);       // [NA][W] the common part of Phi
+    int *s_ped = reinterpret_cast<int *>(lds + a.L.ped);
+    int *s_nsub = reinterpret_cast<int *>(lds + a.L.nsub);
+    int *s_sel = reinterpret_cast<int *>(lds + a.L.sel);               // survivor: parent << 10 | vertex
+    constexpr int URS = 32 * WU + 16;           // stride of a row word over u: the four k-groups on different banks
+
+    const int t0 = threadIdx.x, wid = __builtin_amdgcn_readfirstlane(t0 >> 6);
+    const int sw = wid % SW, uw = wid / SW;
+    uint16_t *phi_g = reinterpret_cast<uint16_t *>(a.ws + (size_t)blockIdx.x * a.ws_stride);   // [n1][KS]
+    const int K = a.K;
+    const Costs c = a.c;
+
+    for (bool first = true;; first = false) {
+        const int t = t0;
+        int item = (int)blockIdx.x;
+        if (!first) {
+            if (t == 0) s_item = pull_item(a.queue, a.nwork);
+            __syncthreads();
+            item = __builtin_amdgcn_readfirstlane(s_item);
+            __syncthreads();
+        }
+        if (item >= a.nwork) break;
+        const WorkItem wi = a.work[item];
+        const GraphRec g1 = a.src.graphs[wi.src];
+        const GraphRec g2 = a.dst.graphs[wi.dst];
+        const int n1 = g1.n, n2 = g2.n, w1 = g1.w, w2 = g2.w;
+        const uint32_t *A1 = a.src.adj + g1.adj;
+        const uint32_t *A2 = a.dst.adj + g2.adj;
+        const int *L1 = a.src.vlab + g1.vlab;
+        const int *L2 = a.dst.vlab + g2.vlab;
+        const int P = a.dst.planes;
+        const size_t pl1 = (size_t)n1 * w1, pl2 = (size_t)n2 * w2;
+        const uint32_t *A1in = A1 + (size_t)(1 + a.src.planes) * pl1;
+        const uint32_t *A2in = A2 + (size_t)(1 + P) * pl2;
+
+        for (int x = t; x < NA * W * URS; x += T) {
+            const int b = x / (W * URS), r = x % (W * URS), kk = r / URS, u = r % URS;
+            const bool in = DIR && kk >= WU;
+            const int kr = in ? kk - WU : kk;
+            s_rows[x] = (u < n2 && kr < w2 && b <= P) ? (in ? A2in : A2)[(size_t)b * pl2 + (size_t)u * w2 + kr] : 0u;
+        }
+        for (int x = t; x < W * KP; x += T) {
+            const int kk = x / KP;
+            s_img[x] = kk < WU ? ~below(n2, kk) : 0u;
+        }
+        for (int x = t; x < NA * W * KP; x += T) s_phi[x] = 0u;
+        for (int x = t; x < (WU + 1) * KP; x += T) {
+            s_le[x] = 0u;
+            s_lt[x] = 0u;
+        }
+        for (int x = t; x < NA * W; x += T) s_pc[x] = 0u;
+        for (int x = t; x < KS; x += T) {
+            s_ped[x] = 0;
+            s_nsub[x] = 0;
+        }
+        if (t == 0) {
+            s_neq = 0;
+            s_sumV[0] = s_sumV[1] = 0;
+            s_min[0] = s_min[1] = 0xffffffffu;
+        }
+        int nb = 1, m0 = 0, V = n2 + 1;
+        int b0 = 0, nblk = 0;       // window blocks [b0, nblk)
+        int dlt = 0, spr = 0;       // last level's T - m0, T - least child
+        long long ce = 0;
+        __syncthreads();
+
+        // image of g1 vertex j under slot s, for j in the window or common
+        auto image = [&](int j, int s) -> uint32_t {
+            if (j >= BL * nblk) return s_cur[(j - BL * nblk) * KS + s];
+            return phi_g[(size_t)j * KS + s_anc[(j / BL) * KS + s]];
+        };
+        // g2 edges (arcs) inside Img of slot us, split over its parts: twice the count
+        auto inside = [&](int s, int part) -> int {
+            uint32_t im[W];
+#pragma unroll
+            for (int k = 0; k < W; ++k) im[k] = s_img[k * KP + s];
+            int e = 0;
+            for (int u = part; u < n2; u += PARTS) {
+                if (!((s_img[(u >> 5) * KP + s] >> (u & 31)) & 1u)) continue;
+#pragma unroll
+                for (int k = 0; k < W; ++k) e += __popc(im[k] & s_rows[k * URS + u]);
+            }
+#pragma unroll
+            for (int o = 1; o < PARTS; o <<= 1) e += __shfl_xor(e, o);
+            return e;
+        };
+
+        for (int i = 0; i < n1; ++i) {
+            // the thread's index is opaque in each level: addresses are formed
+            // where they are used instead of being kept for the whole pair
+            int t = t0;
+            asm volatile("" : "+v"(t));
+            const int lane = t & 63, q = lane >> 4, col = lane & 15;
+            const int us = t / PARTS, part = t % PARTS;   // slot and share of the update's threads
+            const int lab1 = L1[i];
+            const int c0 = BL * b0;
+            const uint32_t *R1 = A1 + (size_t)i * w1, *R1in = A1in + (size_t)i * w1;
+            int degP = 0;
+            for (int kw = 0; kw * 32 < i; ++kw) {
+                degP += __popc(R1[kw] & below(i, kw));
+                if (DIR) degP += __popc(R1in[kw] & below(i, kw));
+            }
+            const int del_cost = c.vdel + c.edel * degP;
+
+            // ---------------- the common part of Phi, the window's neighbours, label costs
+            for (int j = t; j < c0; j += T) {
+                const uint32_t x = s_com[j];
+                for (int d = 0; d < (DIR ? 2 : 1); ++d) {
+                    const uint32_t *R = d ? R1in : R1;
+                    if (x == DEL16 || !((R[j >> 5] >> (j & 31)) & 1u)) continue;
+                    const int xw = (int)(x >> 5) + (d ? WU : 0);
+                    atomicOr(&s_pc[xw], 1u << (x & 31));
+#pragma unroll
+                    for (int b = 1; b < NA; ++b)
+                        if (b <= P && ((R[(size_t)b * pl1 + (j >> 5)] >> (j & 31)) & 1u))
+                            atomicOr(&s_pc[b * W + xw], 1u << (x & 31));
+                }
+            }
+            if (wid == 0) {
+                int base = 0;
+                for (int d = 0; d < (DIR ? 2 : 1); ++d) {
+                    const uint32_t *R = d ? R1in : R1;
+                    for (int kw = c0 >> 5; kw * 32 < i; ++kw) {
+                        const uint32_t bits = R[kw] & below(i, kw) & ~below(c0, kw);
+                        const bool mine = lane < 32 && ((bits >> lane) & 1u);
+                        const unsigned long long m = __ballot(mine);
+                        if (mine) {
+                            const int rank = (int)__builtin_amdgcn_mbcnt_lo((unsigned)m, 0u);
+                            s_nbr[base + rank] = (uint16_t)((kw * 32 + lane) | (d << 15));
+                            if (LAB) {
+                                int code = 0;
+#pragma unroll
+                                for (int b = 1; b < NA; ++b)
+                                    if (b <= P) code |= (int)((R[(size_t)b * pl1 + kw] >> lane) & 1u) << (b - 1);
+                                s_nbc[base + rank] = (uint8_t)code;
+                            }
+                        }
+                        base += __popcll(m);
+                    }
+                }
+                if (lane == 0) s_nw = base;
+            }
+            for (int u = t; u < URS; u += T) {
+                const int lc = (u < n2 && lab1 != L2[u]) ? c.vsub : 0;
+                if (FAST) s_lc[u] = (float)lc;
+                else s_lci[u] = lc;
+            }
+            if (b0 < nblk && us < nb && s_anc[b0 * KS + us] != s_anc[b0 * KS]) s_neq = 1;
+            __syncthreads();
+
+            // ---------------- the window's part of Phi, slot by slot
+            {
+                const int nw = s_nw, slot = t % KS, p0 = t / KS;
+                constexpr int LB = 4;
+                if (slot < nb) {
+                    for (int kb = p0; kb < nw; kb += LB * PARTS) {
+                        uint32_t x[LB];
+                        int nj[LB];
+#pragma unroll
+                        for (int k = 0; k < LB; ++k) {
+                            const int kk = kb + k * PARTS;
+                            nj[k] = kk < nw ? (int)s_nbr[kk] : -1;
+                            x[k] = nj[k] >= 0 ? image(nj[k] & 0x7fff, slot) : DEL16;
+                        }
+#pragma unroll
+                        for (int k = 0; k < LB; ++k) {
+                            if (x[k] == DEL16) continue;
+                            const int xw = (int)(x[k] >> 5) + ((DIR && (nj[k] >> 15)) ? WU : 0);
+                            const uint32_t bit = 1u << (x[k] & 31);
+                            atomicOr(&s_phi[xw * KP + slot], bit);
+                            if (LAB) {
+                                const int code = s_nbc[kb + k * PARTS];
+                                if (code & 1) atomicOr(&s_phi[(W + xw) * KP + slot], bit);
+                                if (code & 2) atomicOr(&s_phi[(2 * W + xw) * KP + slot], bit);
+                            }
+                        }
+                    }
+                }
+                // a block with one ancestor left joins the common mapping
+                if (b0 < nblk && s_neq == 0) {
+                    if (t < BL) s_com[BL * b0 + t] = phi_g[(size_t)(BL * b0 + t) * KS + s_anc[b0 * KS]];
+                    ++b0;
+                }
+            }
+            __syncthreads();
+
+            ce += V;
+            int nb_new;
+            if (a.last_complete && i == n1 - 1) {
+                // ---------------- complete-then-minimum last level: the least
+                // total (Sec. 4.4.1), first in generation order
+                unsigned long long bk = ~0ull;
+                if (us < nb) {
+                    const int e0 = inside(us, part) / 2, ns = s_nsub[us];
+                    for (int u = part; u <= n2; u += PARTS) {
+                        int d = s_ped[us], left = g2.m - e0, used = ns;
+                        if (u < n2) {
+                            if ((s_img[(u >> 5) * KP + us] >> (u & 31)) & 1u) continue;
+                            int kept = 0, inimg = 0, relab = 0;
+                            for (int k = 0; k < W; ++k) {
+                                const uint32_t row = s_rows[k * URS + u];
+                                const uint32_t ph = s_phi[k * KP + us] | s_pc[k];
+                                kept += __popc(ph & row);
+                                inimg += __popc(s_img[k * KP + us] & row);
+                                if (LAB) {
+                                    const uint32_t f0 = (s_phi[(W + k) * KP + us] | s_pc[W + k]) ^ s_rows[(W + k) * URS + u];
+                                    const uint32_t f1 = (s_phi[(2 * W + k) * KP + us] | s_pc[2 * W + k]) ^ s_rows[(2 * W + k) * URS + u];
+                                    relab += __popc(ph & row & (f0 | f1));
+                                }
+                            }
+                            d += (FAST ? (int)s_lc[u] : s_lci[u]) + c.edel * (degP - kept) + c.eins * (inimg - kept) +
+                                 c.esub * relab;
+                            left -= inimg;
+                            ++used;
+                        } else {
+                            d += del_cost;
+                        }
+                        const int total = d + c.vins * (n2 - used) + c.eins * left;
+                        const unsigned long long key = ((unsigned long long)(unsigned)total << 32) |
+                                                       (unsigned)((us << 10) | u);
+                        bk = key < bk ? key : bk;
+                    }
+                }
+                bk = wave_min64(bk);
+                if (lane == 0) s_red64[wid] = bk;
+                __syncthreads();
+                if (t == 0) {
+                    unsigned long long m = s_red64[0];
+#pragma unroll
+                    for (int k = 1; k < NWV; ++k) m = s_red64[k] < m ? s_red64[k] : m;
+                    const int low = (int)(m & 0xffffffffu);
+                    s_sel[0] = (low & 1023) == n2 ? (low | DELU) : low;
+                }
+                nb_new = 1;
+            } else {
+                int quota = 0;
+                if (V <= K) {
+                    // every child survives: the free vertices and the deletion
+                    for (int x = t; x < (WU + 1) * KS; x += T) {
+                        const int k = x / KS, s = x % KS;
+                        if (s < nb) {
+                            const uint32_t m = k < WU ? ~s_img[k * KP + s] : 1u;
+                            s_le[k * KP + s] = m;
+                            s_lt[k * KP + s] = m;
+                        }
+                    }
+                    dlt = spr = 0;
+                } else {
+                    // ---------------- score: bytes of all children, in registers
+                    uint32_t cand[NT][NCAND];
+                    int b = max(m0, m0 + dlt - 63), sh = 0;
+                    int tb = 0;            // threshold byte
+                    bool coarse = false;
+                    for (;;) {
+                        float yminf = FBIG;
+                        int ymini = 0x7fffffff;
+                        const float inv = FAST ? __builtin_ldexpf(1.f, -sh) : 1.f;
+                        const float gi = a.unit * inv;
+                        // the conversion to a byte rounds to nearest: half a
+                        // unit less its own step below makes it a floor
+                        const float bias = FAST ? 0.5f - 0.5f * inv : 0.f;
+                        uint32_t B[NT][NOP][KST][4];
+                        float basef[NT];
+                        int basei[NT];
+#pragma unroll
+                        for (int n = 0; n < NT; ++n) {
+                            const int slot = (sw * NT + n) * 16 + col;
+                            basei[n] = s_ped[slot] + c.edel * degP - b;
+                            basef[n] = slot < nb ? (float)basei[n] * inv - bias : FBIG;
+#pragma unroll
+                            for (int ks = 0; ks < KST; ++ks) {
+                                const int k = 4 * ks + q;
+                                const uint32_t im = s_img[k * KP + slot];
+                                const uint32_t ph = s_phi[k * KP + slot] | s_pc[k];
+                                if (FAST) {
+                                    if (a.code_img == 1 && a.code_phi == 9) {
+#pragma unroll
+                                        for (int j = 0; j < 4; ++j)
+                                            B[n][0][ks][j] = ((im >> j) & NIB) | (((ph >> j) & NIB) << 3);
+                                    } else {
+                                        const uint32_t ao = im & ~ph;
+#pragma unroll
+                                        for (int j = 0; j < 4; ++j)
+                                            B[n][0][ks][j] = ((ao >> j) & NIB) * (uint32_t)a.code_img |
+                                                             ((ph >> j) & NIB) * (uint32_t)a.code_phi;
+                                    }
+                                } else {
+                                    spread(ph, B[n][0][ks]);
+                                    spread(im, B[n][1][ks]);
+                                }
+                                if (LAB) {
+                                    const uint32_t f0 = s_phi[(W + k) * KP + slot] | s_pc[W + k];
+                                    const uint32_t f1 = s_phi[(2 * W + k) * KP + slot] | s_pc[2 * W + k];
+#pragma unroll
+                                    for (int l = 0; l < 4; ++l) {
+                                        const uint32_t m = ph & ((l & 1) ? f0 : ~f0) & ((l & 2) ? f1 : ~f1);
+#pragma unroll
+                                        for (int j = 0; j < 4; ++j)
+                                            B[n][NOP - 4 + l][ks][j] =
+                                                FAST ? ((m >> j) & NIB) * (uint32_t)a.code_same : ((m >> j) & NIB);
+                                    }
+                                }
+                            }
+                        }
+                        // (opaque, so that the tiles' bounds are compared where
+                        // they are needed and not kept for the whole pair)
+                        // (unit matrix of the strike-out step: row `col` of an even tile)
+                        uint32_t e_lo[4];
+                        spread(1u << col, e_lo);
+                        int n2v = __builtin_amdgcn_readfirstlane(n2), qv = q;
+                        asm volatile("" : "+s"(n2v), "+v"(qv));
+#pragma unroll
+                        for (int g = 0; g < (2 * WU + 7) / 8; ++g) {
+                            uint32_t bd[NT][4];
+#pragma unroll
+                            for (int n = 0; n < NT; ++n)
+                                spread(s_img[(4 * g + qv) * KP + (sw * NT + n) * 16 + col], bd[n]);
+#pragma unroll
+                            for (int kk = 0; kk < 8 / UW; ++kk) {
+                                const int k = g * (8 / UW) + kk;   // this wave's k-th target tile
+                                if (k >= NTL) continue;
+                                const int tile = k * UW + uw;
+                                __builtin_amdgcn_sched_barrier(0);   // one tile's operands at a time
+                                if (16 * tile >= n2v) {
+#pragma unroll
+                                    for (int n = 0; n < NT; ++n) cand[n][k] = DEAD;
+                                    continue;
+                                }
+                                uint32_t A[KST][4], Ad[4];
+                                uint32_t rw[KST], rp0[KST], rp1[KST];
+#pragma unroll
+                                for (int ks = 0; ks < KST; ++ks) {
+                                    const int at = (4 * ks + qv) * URS + 16 * tile + col;
+                                    rw[ks] = s_rows[at];
+                                    spread(rw[ks], A[ks]);
+                                    if (LAB) {
+                                        rp0[ks] = s_rows[W * URS + at];
+                                        rp1[ks] = s_rows[2 * W * URS + at];
+                                    }
+                                }
+                                const bool here = qv == ((tile >> 1) & 3);
+#pragma unroll
+                                for (int j = 0; j < 4; ++j) Ad[j] = here ? ((tile & 1) ? e_lo[j] << 16 : e_lo[j]) : 0u;
+                                const v4f lcv = *reinterpret_cast<const v4f *>(&s_lc[16 * tile + 4 * qv]);
+                                if (FAST) {
+                                    v4f acc[NT], dd[NT];
+#pragma unroll
+                                    for (int n = 0; n < NT; ++n) {
+#pragma unroll
+                                        for (int r = 0; r < 4; ++r) dd[n][r] = __builtin_fmaf(lcv[r], inv, basef[n]);
+                                        dd[n] = mfma_fp4(Ad, bd[n], dd[n], SC_BIG);
+                                        acc[n] = v4f{0.f, 0.f, 0.f, 0.f};
+                                    }
+#pragma unroll
+                                    for (int ks = 0; ks < KST; ++ks)
+#pragma unroll
+                                        for (int n = 0; n < NT; ++n) acc[n] = mfma_fp4(A[ks], B[n][0][ks], acc[n], SC_ONE);
+                                    if (LAB) {
+#pragma unroll
+                                        for (int l = 0; l < 4; ++l) {
+                                            if (l >= 2 && P < 2) continue;   // one plane: two codes
+#pragma unroll
+                                            for (int ks = 0; ks < KST; ++ks) {
+                                                uint32_t Al[4];
+                                                spread(rw[ks] & ((l & 1) ? rp0[ks] : ~rp0[ks]) & ((l & 2) ? rp1[ks] : ~rp1[ks]), Al);
+#pragma unroll
+                                                for (int n = 0; n < NT; ++n)
+                                                    acc[n] = mfma_fp4(Al, B[n][NOP - 4 + l][ks], acc[n], SC_ONE);
+                                            }
+                                        }
+                                    }
+#pragma unroll
+                                    for (int n = 0; n < NT; ++n) {
+                                        float y[4];
+                                        uint32_t w = 0u;
+#pragma unroll
+                                        for (int r = 0; r < 4; ++r) y[r] = __builtin_fmaf(acc[n][r], gi, dd[n][r]);
+#pragma unroll
+                                        for (int r = 0; r < 4; ++r) w = __builtin_amdgcn_cvt_pk_u8_f32(fminf(y[r], (float)XCAP), r, w);
+                                        cand[n][k] = w;
+                                        yminf = fminf(yminf, fminf(fminf(y[0], y[1]), fminf(y[2], y[3])));
+                                    }
+                                } else {
+#pragma unroll
+                                    for (int n = 0; n < NT; ++n) {
+                                        v4f z = v4f{0.f, 0.f, 0.f, 0.f};
+                                        const v4f dd = mfma_fp4(Ad, bd[n], z, SC_BIG);
+                                        v4f kp = z, ii = z, sm = z;
+#pragma unroll
+                                        for (int ks = 0; ks < KST; ++ks) {
+                                            kp = mfma_fp4(A[ks], B[n][0][ks], kp, SC_ONE);
+                                            ii = mfma_fp4(A[ks], B[n][1][ks], ii, SC_ONE);
+                                        }
+                                        if (LAB) {
+#pragma unroll
+                                            for (int l = 0; l < 4; ++l)
+#pragma unroll
+                                                for (int ks = 0; ks < KST; ++ks) {
+                                                    uint32_t Al[4];
+                                                    spread(rw[ks] & ((l & 1) ? rp0[ks] : ~rp0[ks]) & ((l & 2) ? rp1[ks] : ~rp1[ks]), Al);
+                                                    sm = mfma_fp4(Al, B[n][NOP - 4 + l][ks], sm, SC_ONE);
+                                                }
+                                        }
+                                        uint32_t w = 0u;
+                                        const bool dead = (sw * NT + n) * 16 + col >= nb;
+#pragma unroll
+                                        for (int r = 0; r < 4; ++r) {
+                                            const int kept = (int)kp[r];
+                                            int y = basei[n] + __float_as_int(lcv[r]) + c.eins * ((int)ii[r] - kept) - c.edel * kept;
+                                            if (LAB) y += c.esub * (kept - (int)sm[r]);
+                                            y = (dead || dd[r] > 0.5f) ? 0x7fffffff : y;
+                                            ymini = min(ymini, y);
+                                            w |= (uint32_t)min(max(y >> sh, 0), XCAP) << (8 * r);
+                                        }
+                                        cand[n][k] = w;
+                                    }
+                                }
+                            }
+                        }
+                        // the deletion children, one byte per slot
+#pragma unroll
+                        for (int n = 0; n < NT; ++n) {
+                            const int slot = (sw * NT + n) * 16 + col;
+                            const bool mine = q == 0 && uw == 0 && slot < nb;
+                            const int y = s_ped[slot] + del_cost - b;
+                            cand[n][NTL] = mine ? (0x7f7f7f00u | (uint32_t)min(max(y >> sh, 0), XCAP)) : DEAD;
+                            if (mine) {
+                                if (FAST) yminf = fminf(yminf, (float)y * inv - bias);
+                                else ymini = min(ymini, y);
+                            }
+                        }
+                        int ylow;   // lower bound of the least byte (exact when sh = 0)
+                        {
+                            const int yl = FAST ? (int)floorf(fminf(yminf, 1.0e6f)) : min(ymini >> sh, 1000000);
+                            const uint32_t wm = wave_umin((uint32_t)yl + 0x40000000u);
+                            if (lane == 0) s_red[0][wid] = wm;
+                            __syncthreads();
+                            uint32_t m = s_red[0][0];
+#pragma unroll
+                            for (int k = 1; k < NWV; ++k) m = min(m, s_red[0][k]);
+                            ylow = (int)(m - 0x40000000u);
+                        }
+
+                        // ---------------- the smallest byte t with at least K children at or below it
+                        int lo = max(sh == 0 ? ylow : ylow - 1, 0), hi = XCAP;
+                        const int off = lo;
+                        int ta = max(min(spr + off, XCAP - 1) - 1, off), tc = min(ta + 1, XCAP - 1);
+                        int par = 1;
+                        for (int s = 1; lo < hi; s <<= 1) {
+                            const uint32_t Ca = ((uint32_t)ta * 0x01010101u) | HI, Cb = ((uint32_t)tc * 0x01010101u) | HI;
+                            uint32_t ca = 0u, cb = 0u;
+#pragma unroll
+                            for (int n = 0; n < NT; ++n)
+#pragma unroll
+                                for (int k = 0; k < NCAND; ++k) {
+                                    ca += (uint32_t)__popc((Ca - cand[n][k]) & HI);
+                                    cb += (uint32_t)__popc((Cb - cand[n][k]) & HI);
+                                }
+                            const uint32_t w = wave_sum(ca | (cb << 16));
+                            if (lane == 0) s_red[par][wid] = w;
+                            __syncthreads();
+                            int na = 0, nc = 0;
+#pragma unroll
+                            for (int k = 0; k < NWV; ++k) {
+                                const uint32_t v = s_red[par][k];
+                                na += (int)(v & 0xffffu);
+                                nc += (int)(v >> 16);
+                            }
+                            par ^= 1;
+                            if (nc >= K) hi = min(hi, tc);
+                            else lo = max(lo, tc + 1);
+                            if (na >= K) hi = min(hi, ta);
+                            else lo = max(lo, ta + 1);
+                            if (lo >= hi) break;
+                            if (hi == XCAP) {
+                                ta = min(lo + s - 1, XCAP - 1);
+                                tc = min(lo + 2 * s, XCAP - 1);
+                            } else if (lo == off) {
+                                tc = hi - 1;
+                                ta = max(hi - 1 - s, off);
+                            } else {
+                                const int span = hi - lo;
+                                ta = lo + (span - 1) / 3;
+                                tc = lo + (2 * span - 1) / 3;
+                            }
+                        }
+                        __syncthreads();   // the last round's sums are read before the next pass writes
+                        // exact when the range is exact and T lies inside it
+                        // (byte 0 also stands for children below b)
+                        if (sh == 0 && lo < XCAP && (lo > 0 || ylow >= 0)) {
+                            tb = lo;
+                            dlt = b + tb - m0;
+                            spr = tb - ylow;
+                            break;
+                        }
+                        if (!coarse) {
+                            coarse = true;
+                            b = m0;
+                            sh = 0;
+                            while (((a.pedbound - (uint32_t)m0) >> sh) >= (uint32_t)XCAP) ++sh;
+                        } else {
+                            // bucket `lo` becomes the range, one byte up: byte 0 takes what is below it
+                            const int sn = max(sh - 6, 0);
+                            b += (lo << sh) - (1 << sn);
+                            sh = sn;
+                        }
+                        spr = 0;
+                    }
+
+                    // ---------------- survivors' bits
+                    const uint32_t Cle = ((uint32_t)tb * 0x01010101u) | HI;
+                    const uint32_t Clt = tb > 0 ? (((uint32_t)tb - 1u) * 0x01010101u) | HI : DEAD;
+#pragma unroll
+                    for (int n = 0; n < NT; ++n) {
+                        const int slot = (sw * NT + n) * 16 + col;
+#pragma unroll
+                        for (int k = 0; k < NCAND; ++k) {
+                            const uint32_t fle = (Cle - cand[n][k]) & HI;
+                            if (fle) {
+                                const uint32_t flt = (Clt - cand[n][k]) & HI;
+                                const int tile = k * UW + uw;
+                                const int row = k < NTL ? (tile >> 1) * KP + slot : WU * KP + slot;
+                                const int shf = k < NTL ? 16 * (tile & 1) + 4 * q : 0;
+                                atomicOr(&s_le[row], (__builtin_amdgcn_udot4(fle, 0x08040201u, 0u, false) >> 7) << shf);
+                                if (flt)
+                                    atomicOr(&s_lt[row], (__builtin_amdgcn_udot4(flt, 0x08040201u, 0u, false) >> 7) << shf);
+                            }
+                        }
+                    }
+                }
+                __syncthreads();
+
+                // ---------------- emission in generation order: slot, vertex, the deletion last
+                // (the first KS / 64 waves, a slot per lane)
+                int lt = 0, eq = 0, LT = 0, EQ = 0;
+                if (t < (KS < 64 ? 64 : KS)) {
+                    const int s = t;
+                    if (s < KS) {
+#pragma unroll
+                        for (int k = 0; k <= WU; ++k) {
+                            lt += __popc(s_lt[k * KP + s]);
+                            eq += __popc(s_le[k * KP + s]);
+                        }
+                    }
+                    eq -= lt;
+                    LT = wave_excl_scan(lt);
+                    EQ = wave_excl_scan(eq);
+                    if (KS > 64 && lane == 63) {
+                        s_red[0][wid] = (uint32_t)(LT + lt);
+                        s_red[1][wid] = (uint32_t)(EQ + eq);
+                    }
+                }
+                int allt = 0;
+                if (KS > 64) {
+                    __syncthreads();
+                    if (t < KS) {
+#pragma unroll
+                        for (int k = 0; k < KS / 64; ++k) {
+                            const int x = (int)s_red[0][k], y = (int)s_red[1][k];
+                            LT += k < wid ? x : 0;
+                            EQ += k < wid ? y : 0;
+                            allt += x;
+                        }
+                    }
+                } else if (t < 64) {
+                    allt = __builtin_amdgcn_readlane(LT + lt, 63);
+                }
+                nb_new = min(V, K);
+                if (t < KS && lt + eq > 0) {
+                    quota = nb_new - allt;          // ties at T that survive
+                    const int eqb = min(EQ, quota); // ... of the slots before
+                    int keq = min(quota - eqb, eq);
+                    int pos = LT + eqb;
+#pragma unroll 1
+                    for (int k = 0; k <= WU; ++k) {
+                        uint32_t m = s_le[k * KP + t];
+                        if (!m) continue;
+                        const uint32_t ml = s_lt[k * KP + t];
+                        while (m) {
+                            const uint32_t bit = m & (0u - m);
+                            m ^= bit;
+                            if (!(ml & bit)) {
+                                if (keq == 0) continue;
+                                --keq;
+                            }
+                            s_sel[pos++] = (t << 10) | (k < WU ? 32 * k + (int)__builtin_ctz(bit) : DELU);
+                        }
+                    }
+                }
+            }
+            __syncthreads();
+
+            // ---------------- update: the new slots gather their parents' state ...
+            const int par = i & 1;
+            const bool live = us < nb_new;
+            int p = 0, u = DELU, nped = 0, nns = 0;
+            uint32_t nim[NWP];
+            uint16_t cv[(BL + PARTS - 1) / PARTS];
+            const int r8 = i % BL;      // row of this level in its block
+            if (live) {
+                const int sel = s_sel[us];
+                p = sel >> 10;
+                u = sel & 1023;
+            }
+            const bool sub = u < n2;
+            {
+                int kept = 0, inimg = 0, relab = 0;
+#pragma unroll
+                for (int k = 0; k < NWP; ++k) {
+                    const int w = part + k * PARTS;
+                    nim[k] = 0u;
+                    if (w < W && live) {
+                        const uint32_t im = s_img[w * KP + p];
+                        nim[k] = im;
+                        if (sub) {
+                            const uint32_t row = s_rows[w * URS + u];
+                            const uint32_t ph = s_phi[w * KP + p] | s_pc[w];
+                            kept += __popc(ph & row);
+                            inimg += __popc(im & row);
+                            if (LAB) {
+                                const uint32_t f0 = (s_phi[(W + w) * KP + p] | s_pc[W + w]) ^ s_rows[(W + w) * URS + u];
+                                const uint32_t f1 = (s_phi[(2 * W + w) * KP + p] | s_pc[2 * W + w]) ^ s_rows[(2 * W + w) * URS + u];
+                                relab += __popc(ph & row & (f0 | f1));
+                            }
+                            if (w == (u >> 5) || (DIR && w == (u >> 5) + WU)) nim[k] |= 1u << (u & 31);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int o = 1; o < PARTS; o <<= 1) {
+                    kept += __shfl_xor(kept, o);
+                    inimg += __shfl_xor(inimg, o);
+                    if (LAB) relab += __shfl_xor(relab, o);
+                }
+                if (live) {
+                    nped = s_ped[p];
+                    nns = s_nsub[p] + (sub ? 1 : 0);
+                    if (sub)
+                        nped += (FAST ? (int)s_lc[u] : s_lci[u]) + c.edel * (degP - kept) + c.eins * (inimg - kept) +
+                                c.esub * relab;
+                    else
+                        nped += del_cost;
+#pragma unroll
+                    for (int k = 0; k < (BL + PARTS - 1) / PARTS; ++k) {
+                        const int r = part + k * PARTS;
+                        cv[k] = r < r8 ? s_cur[r * KS + p] : (uint16_t)0;
+                    }
+                }
+                const int vs = wave_sum((live && part == 0) ? (uint32_t)(n2 - nns + 1) : 0u);
+                const uint32_t mn = wave_umin((live && part == 0) ? (uint32_t)nped : 0xffffffffu);
+                if (lane == 0) {
+                    atomicAdd(&s_sumV[par], vs);
+                    atomicMin(&s_min[par], mn);
+                }
+            }
+            // ... and write it, all at once (the ancestor rows in steps)
+            uint16_t av[MAXA];
+            bool rest = true;
+            for (int g = b0; rest; g += MAXA * PARTS) {
+#pragma unroll
+                for (int k = 0; k < MAXA; ++k) {
+                    const int r = g + part + k * PARTS;
+                    av[k] = (r < nblk && live) ? s_anc[r * KS + p] : (uint16_t)0;
+                }
+                __syncthreads();
+                if (g == b0) {
+                    if (live) {
+#pragma unroll
+                        for (int k = 0; k < NWP; ++k)
+                            if (part + k * PARTS < W) s_img[(part + k * PARTS) * KP + us] = nim[k];
+                        const uint16_t xi = sub ? (uint16_t)u : (uint16_t)DEL16;
+                        const bool full = r8 == BL - 1;
+#pragma unroll
+                        for (int k = 0; k < (BL + PARTS - 1) / PARTS; ++k) {
+                            const int r = part + k * PARTS;
+                            if (r > r8) continue;
+                            const uint16_t x = r == r8 ? xi : cv[k];
+                            if (full) phi_g[(size_t)(i - r8 + r) * KS + us] = x;
+                            else s_cur[r * KS + us] = x;
+                        }
+                        if (part == 0) {
+                            s_ped[us] = nped;
+                            s_nsub[us] = nns;
+                            if (full) s_anc[nblk * KS + us] = (uint16_t)us;
+                        }
+                    }
+#pragma unroll
+                    for (int k = 0; k < NWP; ++k) {
+                        const int w = part + k * PARTS;
+                        if (w < W) {
+#pragma unroll
+                            for (int b = 0; b < NA; ++b) s_phi[(b * W + w) * KP + us] = 0u;
+                        }
+                    }
+                    for (int w = part; w <= WU; w += PARTS) {
+                        s_le[w * KP + us] = 0u;
+                        s_lt[w * KP + us] = 0u;
+                    }
+                    if (t < NA * W) s_pc[t] = 0u;
+                    if (t == 0) {
+                        s_neq = 0;
+                        s_sumV[par ^ 1] = 0;
+                        s_min[par ^ 1] = 0xffffffffu;
+                    }
+                }
+                if (live) {
+#pragma unroll
+                    for (int k = 0; k < MAXA; ++k) {
+                        const int r = g + part + k * PARTS;
+                        if (r < nblk) s_anc[r * KS + us] = av[k];
+                    }
+                }
+                rest = g + MAXA * PARTS < nblk;
+            }
+            if (r8 == BL - 1) ++nblk;
+            nb = nb_new;
+            __syncthreads();
+            V = s_sumV[par];
+            m0 = (int)s_min[par];
+        }
+
+        // ---------------- completion: insert what is left of g2, pick the best leaf
+        const int us = t / PARTS, part = t % PARTS;
+        unsigned long long best = ~0ull;
+        if (us < nb) {
+            const int e2 = inside(us, part);
+            const int total = s_ped[us] + c.vins * (n2 - s_nsub[us]) + c.eins * (g2.m - e2 / 2);
+            best = ((unsigned long long)(unsigned)total << 32) | (unsigned)us;
+        }
+        best = wave_min64(best);
+        if ((t & 63) == 0) s_red64[wid] = best;
+        __syncthreads();
+        best = s_red64[0];
+#pragma unroll
+        for (int k = 1; k < NWV; ++k) best = s_red64[k] < best ? s_red64[k] : best;
+        const int bs = (int)(best & 0xffffffffu);
+        if (t == 0) {
+            a.out.dist[wi.out] = (int)(best >> 32);
+            if (a.out.cand) a.out.cand[wi.out] = ce;
+        }
+        for (int j = t; j < n1; j += T) {
+            const uint32_t x = j < BL * b0 ? (uint32_t)s_com[j] : image(j, bs);
+            a.out.map[wi.map_off + j] = x == DEL16 ? -1 : (int)x;
+        }
+        __syncthreads();
+    }
+}
+
+struct MatConfig {
+    int W = 0, NT = 0, SW = 0, UW = 0;   // W == 0: no instantiation
+};
+
+template <bool LAB, bool DIR, bool FAST>
+const void *mat_select(const MatConfig &m) {
+#define GEDK_M(w, nt, sw, uw)                                  \
+    if (m.W == w && m.NT == nt && m.SW == sw && m.UW == uw)     \
+        return reinterpret_cast<const void *>(&kb_mat_kernel<w, nt, sw, uw, LAB, DIR, FAST>);
+#define GEDK_MW(nt, sw, uw) GEDK_M(4, nt, sw, uw) GEDK_M(8, nt, sw, uw) GEDK_M(16, nt, sw, uw)
+    GEDK_MW(1, 1, 4) GEDK_MW(1, 2, 2) GEDK_MW(1, 4, 1) GEDK_MW(1, 4, 2) GEDK_MW(1, 8, 1) GEDK_MW(2, 8, 1)
+    GEDK_M(4, 4, 8, 1) GEDK_M(8, 4, 8, 1) GEDK_M(4, 4, 16, 1)
+#undef GEDK_MW
+#undef GEDK_M
+    return nullptr;
+}
+
+// The instantiations for undirected / directed graphs without / with edge
+// labels, each in a source of its own.
+const void *mat_kernel_plain(const MatConfig &m, bool fast);
+const void *mat_kernel_lab(const MatConfig &m, bool fast);
+const void *mat_kernel_dir(const MatConfig &m, bool fast);
+const void *mat_kernel_dir_lab(const MatConfig &m, bool fast);
+
+}  // namespace mat
+}  // namespace gedk
