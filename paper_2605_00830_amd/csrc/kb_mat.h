@@ -63,14 +63,50 @@ constexpr uint32_t DEL16 = 0xffffu;
 constexpr int XCAP = 127;                   // byte of a child above the range
 constexpr int DELU = 1023;                  // survivor record's vertex of the deletion child
 constexpr int BL = 8;                       // levels per mapping block
-constexpr int SC_ONE = 128;                 // E8M0 scale 2: a 0.5 becomes 1
-constexpr int SC_BIG = 127 + 25;            // a 0.5 becomes 2^24
+constexpr int SC_ONE = 127;                 // E8M0 scales 1, 2^24
+constexpr int SC_BIG = 127 + 24;
+constexpr uint32_t CODE_ONE = 0x4124u;      // slot operand's nibbles of weight 1 (spread_slot)
 constexpr float FBIG = 16777216.f;
 constexpr int64_t kFastBound = (int64_t)1 << 22;   // PEDs below this stay exact in f32 with 1 / 2^sh parts
 
+// Slot stride of the LDS arrays: the four k-groups of an operand on different banks.
+constexpr int slot_pad(int KS) { return KS % 64 == 0 ? KS + 16 : (KS == 32 ? 48 : KS); }
+
+// Byte offsets in dynamic LDS, constants of an instantiation (a row of W words,
+// KS slots, NA sets, ND rows of a vertex); the ancestor rows, whose number goes
+// with the largest source, come last.
 struct MatLds {
-    int rows, lc, img, phi, le, lt, anc, cur, com, nbr, nbc, pc, ped, nsub, sel, bytes;
+    int rows, lc, l1, l2, r1, img, phi, le, lt, cur, com, nbr, nbc, pc, ped, nsub, sel, anc;
 };
+constexpr MatLds mat_lds(int W, int KS, int NA, int ND) {
+    MatLds L{};
+    const int WU = W / ND, URS = 32 * WU + 16, KP = slot_pad(KS), N1 = GED_MAX_VERTICES_BATCH;
+    int off = 0;
+    auto take = [&off](int bytes) {
+        const int o = off;
+        off += (bytes + 15) & ~15;
+        return o;
+    };
+    L.rows = take(NA * W * URS * 4);
+    L.lc = take(URS * 4);
+    L.l1 = take(N1 * 4);
+    L.l2 = take(URS * 4);
+    L.r1 = take(2 * ND * NA * (N1 / 32) * 4);
+    L.img = take(W * KP * 4);
+    L.phi = take(NA * W * KP * 4);
+    L.le = take((WU + 1) * KP * 4);
+    L.lt = take((WU + 1) * KP * 4);
+    L.cur = take(BL * KS * 2);
+    L.com = take(N1 * 2);
+    L.nbr = take(N1 * ND * 2);
+    L.nbc = NA > 1 ? take(N1 * ND) : off;
+    L.pc = take(NA * W * 4);
+    L.ped = take(KS * 4);
+    L.nsub = take(KS * 4);
+    L.sel = take(KS * 4);
+    L.anc = off;
+    return L;
+}
 
 struct MatArgs {
     DbView src, dst;
@@ -82,28 +118,46 @@ struct MatArgs {
     int last_complete;
     char *ws;
     size_t ws_stride;
-    MatLds L;
     Outputs out;
     uint32_t pedbound;   // no PED of the launch exceeds it
-    // FAST: fp4 codes of the slot operand (Img \ Phi, Phi, Phi_c) and their unit
-    int code_img, code_phi, code_same;
-    float unit;
+    // FAST: the slot operand's nibbles (spread_slot) for Img \ Phi, Phi, Phi_c,
+    // and the power of two (E8M0) of their unit
+    uint32_t code_img, code_phi, code_same;
+    int unit_exp;
 };
 
 // One chain step; the operands' scales are E8M0 bytes.
-__device__ __forceinline__ v4f mfma_fp4(const uint32_t (&a)[4], const uint32_t (&b)[4], v4f c, int sa) {
+__device__ __forceinline__ v4f mfma_fp4(const uint32_t (&a)[4], const uint32_t (&b)[4], v4f c, int sa, int sb) {
     v8i x = {}, y = {};
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         x[j] = (int)a[j];
         y[j] = (int)b[j];
     }
-    return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(x, y, c, 4, 4, 0, sa, 0, SC_ONE);
+    return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(x, y, c, 4, 4, 0, sa, 0, sb);
 }
 
-__device__ __forceinline__ void spread(uint32_t w, uint32_t (&e)[4]) {
+// The 32 bits of w as fp4 numbers, bit i in register i % 4.  The row side
+// leaves the bits where they are, so that a word takes five instructions
+// instead of seven: they stand for 0.5, 1, 2 and (shifted down) 0.5 ...
+__device__ __forceinline__ void spread_row(uint32_t w, uint32_t (&e)[4]) {
+    e[0] = w & NIB;
+    e[1] = w & (NIB << 1);
+    e[2] = w & (NIB << 2);
+    e[3] = (w >> 3) & NIB;
+}
+// ... and the slot side makes up for it: a weight m is 2 m, m, m / 2 and 2 m
+// (fp4 has them for m = 0 .. 3), nibble j of `code` for register j.
+__device__ __forceinline__ void spread_slot(uint32_t w, uint32_t code, uint32_t (&e)[4]) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) e[j] = (w >> j) & NIB;
+    for (int j = 0; j < 4; ++j) e[j] = ((w >> j) & NIB) * ((code >> (4 * j)) & 15u);
+}
+// (weight 1)
+__device__ __forceinline__ void spread_one(uint32_t w, uint32_t (&e)[4]) {
+    e[0] = (w << 2) & (NIB << 2);
+    e[1] = w & (NIB << 1);
+    e[2] = (w >> 2) & NIB;
+    e[3] = (w >> 1) & (NIB << 2);
 }
 
 __device__ __forceinline__ uint32_t below(int i, int kw) {
@@ -122,7 +176,10 @@ __device__ __forceinline__ unsigned long long wave_min64(unsigned long long v) {
 
 // W: words of a row (directed: out-half, then in-half); a wave holds NT tiles
 // of 16 slots; SW waves split the slots, UW the target tiles.
-template <int W, int NT, int SW, int UW, bool LAB, bool DIR, bool FAST, int MINW = 2>
+// MINW: waves per SIMD the registers are held to, four where that costs no
+// spills, so that two 512-thread workgroups fit a CU.
+template <int W, int NT, int SW, int UW, bool LAB, bool DIR, bool FAST,
+          int MINW = (FAST && NT == 1 && (W == 4 || (W == 8 && !LAB))) ? 4 : 2>
 __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
     constexpr int KS = 16 * NT * SW;            // slots
     constexpr int T = 64 * SW * UW;
@@ -131,8 +188,11 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
     constexpr int KST = W / 4;                  // 128-vertex steps of a contraction
     constexpr int WU = DIR ? W / 2 : W;         // words that name target vertices
     constexpr int NTL = 2 * WU / UW;            // target tiles of a wave
-    constexpr int KP = KS % 64 == 0 ? KS + 16 : (KS == 32 ? 48 : KS);   // slot stride: the four k-groups on different banks
+    constexpr int KP = slot_pad(KS);
     constexpr int NA = LAB ? 3 : 1;             // sets: Phi / rows, and two label planes
+    constexpr int ND = DIR ? 2 : 1;             // rows of a vertex (out, in)
+    constexpr int W1 = GED_MAX_VERTICES_BATCH / 32;   // words of a source row
+    constexpr int CW = (WU + PARTS) / PARTS;    // mask words of an emitting thread
     constexpr int NS = LAB ? 5 : (FAST ? 1 : 2);   // slot operands (FAST: combined first; else Phi, Img first)
     constexpr int NOP = LAB ? (FAST ? 5 : 6) : NS; // ... with four label codes after them
     constexpr int NCAND = NTL + 1;              // words of a slot tile: target tiles, then the deletion
@@ -140,33 +200,37 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
     constexpr int MAXA = 16;                    // ancestor rows a thread moves per step
     static_assert(W % 4 == 0 && KS <= T && 8 % UW == 0 && (2 * WU) % UW == 0, "shape");
 
+    constexpr MatLds L = mat_lds(W, KS, NA, ND);
     extern __shared__ uint32_t s_dyn[];
     __shared__ uint32_t s_red[2][NWV];
     __shared__ unsigned long long s_red64[NWV];
-    __shared__ int s_item, s_neq, s_nw;
+    __shared__ int s_item, s_neq, s_nw[2];
     __shared__ int s_sumV[2];
     __shared__ uint32_t s_min[2];
     char *lds = reinterpret_cast<char *>(s_dyn);
-    uint32_t *s_rows = reinterpret_cast<uint32_t *>(lds + a.L.rows);   // [NA][W][urs]
-    float *s_lc = reinterpret_cast<float *>(lds + a.L.lc);             // label cost of u (FAST: float, else int bits)
-    int *s_lci = reinterpret_cast<int *>(lds + a.L.lc);
-    uint32_t *s_img = reinterpret_cast<uint32_t *>(lds + a.L.img);     // [W][KP]; bits >= n2 set: never free
-    uint32_t *s_phi = reinterpret_cast<uint32_t *>(lds + a.L.phi);     // [NA][W][KP] the window's part of Phi
-    uint32_t *s_le = reinterpret_cast<uint32_t *>(lds + a.L.le);       // [WU + 1][KP] children at most T (last: deletion)
-    uint32_t *s_lt = reinterpret_cast<uint32_t *>(lds + a.L.lt);       // ... below T
-    uint16_t *s_anc = reinterpret_cast<uint16_t *>(lds + a.L.anc);     // [blocks][KS]
-    uint16_t *s_cur = reinterpret_cast<uint16_t *>(lds + a.L.cur);     // [BL][KS]
-    uint16_t *s_com = reinterpret_cast<uint16_t *>(lds + a.L.com);     // common mapping
-    uint16_t *s_nbr = reinterpret_cast<uint16_t *>(lds + a.L.nbr);     // window neighbours of v_i (bit 15: in-arc)
-    uint8_t *s_nbc = reinterpret_cast<uint8_t *>(lds + a.L.nbc);       // their label codes
-    uint32_t *s_pc = reinterpret_cast<uint32_t *>(lds + a.L.pc);       // [NA][W] the common part of Phi
-    int *s_ped = reinterpret_cast<int *>(lds + a.L.ped);
-    int *s_nsub = reinterpret_cast<int *>(lds + a.L.nsub);
-    int *s_sel = reinterpret_cast<int *>(lds + a.L.sel);               // survivor: parent << 10 | vertex
+    uint32_t *s_rows = reinterpret_cast<uint32_t *>(lds + L.rows);   // [NA][W][urs]
+    float *s_lc = reinterpret_cast<float *>(lds + L.lc);             // label cost of u (FAST: float, else int bits)
+    int *s_lci = reinterpret_cast<int *>(lds + L.lc);
+    int *s_l1 = reinterpret_cast<int *>(lds + L.l1);                 // vertex labels of g1, g2
+    int *s_l2 = reinterpret_cast<int *>(lds + L.l2);
+    uint32_t *s_r1 = reinterpret_cast<uint32_t *>(lds + L.r1);       // [2][ND * NA][W1] row of v_i, by level parity
+    uint32_t *s_img = reinterpret_cast<uint32_t *>(lds + L.img);     // [W][KP]; bits >= n2 set: never free
+    uint32_t *s_phi = reinterpret_cast<uint32_t *>(lds + L.phi);     // [NA][W][KP] the window's part of Phi
+    uint32_t *s_le = reinterpret_cast<uint32_t *>(lds + L.le);       // [WU + 1][KP] children at most T (last: deletion)
+    uint32_t *s_lt = reinterpret_cast<uint32_t *>(lds + L.lt);       // ... below T
+    uint16_t *s_anc = reinterpret_cast<uint16_t *>(lds + L.anc);     // [blocks][KS]
+    uint16_t *s_cur = reinterpret_cast<uint16_t *>(lds + L.cur);     // [BL][KS]
+    uint16_t *s_com = reinterpret_cast<uint16_t *>(lds + L.com);     // common mapping
+    uint16_t *s_nbr = reinterpret_cast<uint16_t *>(lds + L.nbr);     // window neighbours of v_i (bit 15: in-arc)
+    uint8_t *s_nbc = reinterpret_cast<uint8_t *>(lds + L.nbc);       // their label codes
+    uint32_t *s_pc = reinterpret_cast<uint32_t *>(lds + L.pc);       // [NA][W] the common part of Phi
+    int *s_ped = reinterpret_cast<int *>(lds + L.ped);
+    int *s_nsub = reinterpret_cast<int *>(lds + L.nsub);
+    int *s_sel = reinterpret_cast<int *>(lds + L.sel);               // survivor: parent << 10 | vertex
     constexpr int URS = 32 * WU + 16;           // stride of a row word over u: the four k-groups on different banks
 
     const int t0 = threadIdx.x, wid = __builtin_amdgcn_readfirstlane(t0 >> 6);
-    const int sw = wid % SW, uw = wid / SW;
+    const int sw = wid % SW, uw = UW == 1 ? 0 : wid / SW;
     uint16_t *phi_g = reinterpret_cast<uint16_t *>(a.ws + (size_t)blockIdx.x * a.ws_stride);   // [n1][KS]
     const int K = a.K;
     const Costs c = a.c;
@@ -200,6 +264,14 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
             const int kr = in ? kk - WU : kk;
             s_rows[x] = (u < n2 && kr < w2 && b <= P) ? (in ? A2in : A2)[(size_t)b * pl2 + (size_t)u * w2 + kr] : 0u;
         }
+        for (int x = t; x < URS; x += T) s_l2[x] = x < n2 ? L2[x] : 0;
+        for (int x = t; x < n1; x += T) s_l1[x] = L1[x];
+        // word k of set b (row, label planes) of g1 vertex v's out- or in-row
+        auto source_word = [&](int v, int x) -> uint32_t {
+            const int k = x % W1, b = x / W1 % NA, d = x / (W1 * NA);
+            return (v < n1 && k < w1 && b <= P) ? (d ? A1in : A1)[(size_t)b * pl1 + (size_t)v * w1 + k] : 0u;
+        };
+        for (int x = t; x < ND * NA * W1; x += T) s_r1[x] = source_word(0, x);
         for (int x = t; x < W * KP; x += T) {
             const int kk = x / KP;
             s_img[x] = kk < WU ? ~below(n2, kk) : 0u;
@@ -253,56 +325,64 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
             asm volatile("" : "+v"(t));
             const int lane = t & 63, q = lane >> 4, col = lane & 15;
             const int us = t / PARTS, part = t % PARTS;   // slot and share of the update's threads
-            const int lab1 = L1[i];
             const int c0 = BL * b0;
-            const uint32_t *R1 = A1 + (size_t)i * w1, *R1in = A1in + (size_t)i * w1;
+            const int lab1 = s_l1[i];
+            const uint32_t *R1 = s_r1 + (i & 1) * (ND * NA * W1);
+            // the next vertex's row, in flight during the level
+            const uint32_t rown = t < ND * NA * W1 ? source_word(i + 1, t) : 0u;
             int degP = 0;
-            for (int kw = 0; kw * 32 < i; ++kw) {
-                degP += __popc(R1[kw] & below(i, kw));
-                if (DIR) degP += __popc(R1in[kw] & below(i, kw));
+            if (lane < W1) {
+                degP = __popc(R1[lane] & below(i, lane));
+                if (DIR) degP += __popc(R1[NA * W1 + lane] & below(i, lane));
             }
+            degP = (int)wave_sum((uint32_t)degP);
             const int del_cost = c.vdel + c.edel * degP;
 
             // ---------------- the common part of Phi, the window's neighbours, label costs
             for (int j = t; j < c0; j += T) {
                 const uint32_t x = s_com[j];
-                for (int d = 0; d < (DIR ? 2 : 1); ++d) {
-                    const uint32_t *R = d ? R1in : R1;
-                    if (x == DEL16 || !((R[j >> 5] >> (j & 31)) & 1u)) continue;
+#pragma unroll
+                for (int d = 0; d < ND; ++d) {
+                    const uint32_t *R = R1 + d * (NA * W1) + (j >> 5);
+                    if (x == DEL16 || !((R[0] >> (j & 31)) & 1u)) continue;
                     const int xw = (int)(x >> 5) + (d ? WU : 0);
                     atomicOr(&s_pc[xw], 1u << (x & 31));
 #pragma unroll
                     for (int b = 1; b < NA; ++b)
-                        if (b <= P && ((R[(size_t)b * pl1 + (j >> 5)] >> (j & 31)) & 1u))
-                            atomicOr(&s_pc[b * W + xw], 1u << (x & 31));
+                        if ((R[b * W1] >> (j & 31)) & 1u) atomicOr(&s_pc[b * W + xw], 1u << (x & 31));
                 }
             }
-            if (wid == 0) {
+            if (wid == NWV - 1) {
+                // images in the complete blocks first, then those of the current one
                 int base = 0;
-                for (int d = 0; d < (DIR ? 2 : 1); ++d) {
-                    const uint32_t *R = d ? R1in : R1;
-                    for (int kw = c0 >> 5; kw * 32 < i; ++kw) {
-                        const uint32_t bits = R[kw] & below(i, kw) & ~below(c0, kw);
-                        const bool mine = lane < 32 && ((bits >> lane) & 1u);
-                        const unsigned long long m = __ballot(mine);
-                        if (mine) {
-                            const int rank = (int)__builtin_amdgcn_mbcnt_lo((unsigned)m, 0u);
-                            s_nbr[base + rank] = (uint16_t)((kw * 32 + lane) | (d << 15));
-                            if (LAB) {
-                                int code = 0;
+#pragma unroll 1
+                for (int part2 = 0; part2 < 2; ++part2) {
+                    const int jl = part2 ? BL * nblk : c0, jh = part2 ? i : BL * nblk;
 #pragma unroll
-                                for (int b = 1; b < NA; ++b)
-                                    if (b <= P) code |= (int)((R[(size_t)b * pl1 + kw] >> lane) & 1u) << (b - 1);
-                                s_nbc[base + rank] = (uint8_t)code;
+                    for (int d = 0; d < ND; ++d) {
+                        for (int kw = jl >> 5; kw * 32 < jh; ++kw) {
+                            const uint32_t *R = R1 + d * (NA * W1) + kw;
+                            const uint32_t bits = R[0] & below(jh, kw) & ~below(jl, kw);
+                            const bool mine = lane < 32 && ((bits >> lane) & 1u);
+                            const unsigned long long m = __ballot(mine);
+                            if (mine) {
+                                const int rank = (int)__builtin_amdgcn_mbcnt_lo((unsigned)m, 0u);
+                                s_nbr[base + rank] = (uint16_t)((kw * 32 + lane) | (d << 15));
+                                if (LAB) {
+                                    int code = 0;
+#pragma unroll
+                                    for (int b = 1; b < NA; ++b) code |= (int)((R[b * W1] >> lane) & 1u) << (b - 1);
+                                    s_nbc[base + rank] = (uint8_t)code;
+                                }
                             }
+                            base += __popcll(m);
                         }
-                        base += __popcll(m);
                     }
+                    if (lane == 0) s_nw[part2] = base;
                 }
-                if (lane == 0) s_nw = base;
             }
             for (int u = t; u < URS; u += T) {
-                const int lc = (u < n2 && lab1 != L2[u]) ? c.vsub : 0;
+                const int lc = (u < n2 && lab1 != s_l2[u]) ? c.vsub : 0;
                 if (FAST) s_lc[u] = (float)lc;
                 else s_lci[u] = lc;
             }
@@ -311,30 +391,38 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
 
             // ---------------- the window's part of Phi, slot by slot
             {
-                const int nw = s_nw, slot = t % KS, p0 = t / KS;
-                constexpr int LB = 4;
+                const int nwb = s_nw[0], nw = s_nw[1], slot = t % KS, p0 = t / KS;
+                auto mark = [&](uint32_t x, int nj, int at) {
+                    if (x == DEL16) return;   // deleted, or past the list
+                    const int xw = (int)(x >> 5) + ((DIR && (nj >> 15)) ? WU : 0);
+                    const uint32_t bit = 1u << (x & 31);
+                    atomicOr(&s_phi[xw * KP + slot], bit);
+                    if (LAB) {
+                        const int code = s_nbc[at];
+                        if (code & 1) atomicOr(&s_phi[(W + xw) * KP + slot], bit);
+                        if (code & 2) atomicOr(&s_phi[(2 * W + xw) * KP + slot], bit);
+                    }
+                };
+                // (LB rows of the complete blocks in flight together)
+                constexpr int LB = PARTS >= 4 ? 4 : 8;
                 if (slot < nb) {
-                    for (int kb = p0; kb < nw; kb += LB * PARTS) {
+                    for (int kb = p0; kb < nwb; kb += LB * PARTS) {
                         uint32_t x[LB];
                         int nj[LB];
 #pragma unroll
                         for (int k = 0; k < LB; ++k) {
                             const int kk = kb + k * PARTS;
-                            nj[k] = kk < nw ? (int)s_nbr[kk] : -1;
-                            x[k] = nj[k] >= 0 ? image(nj[k] & 0x7fff, slot) : DEL16;
+                            nj[k] = s_nbr[min(kk, nwb - 1)];
+                            const int j = nj[k] & 0x7fff;
+                            x[k] = phi_g[(size_t)j * KS + s_anc[(j / BL) * KS + slot]];
+                            x[k] = kk < nwb ? x[k] : DEL16;
                         }
 #pragma unroll
-                        for (int k = 0; k < LB; ++k) {
-                            if (x[k] == DEL16) continue;
-                            const int xw = (int)(x[k] >> 5) + ((DIR && (nj[k] >> 15)) ? WU : 0);
-                            const uint32_t bit = 1u << (x[k] & 31);
-                            atomicOr(&s_phi[xw * KP + slot], bit);
-                            if (LAB) {
-                                const int code = s_nbc[kb + k * PARTS];
-                                if (code & 1) atomicOr(&s_phi[(W + xw) * KP + slot], bit);
-                                if (code & 2) atomicOr(&s_phi[(2 * W + xw) * KP + slot], bit);
-                            }
-                        }
+                        for (int k = 0; k < LB; ++k) mark(x[k], nj[k], kb + k * PARTS);
+                    }
+                    for (int kk = nwb + p0; kk < nw; kk += PARTS) {
+                        const int nj = s_nbr[kk];
+                        mark(s_cur[((nj & 0x7fff) - BL * nblk) * KS + slot], nj, kk);
                     }
                 }
                 // a block with one ancestor left joins the common mapping
@@ -416,7 +504,7 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
                         float yminf = FBIG;
                         int ymini = 0x7fffffff;
                         const float inv = FAST ? __builtin_ldexpf(1.f, -sh) : 1.f;
-                        const float gi = a.unit * inv;
+                        const int sc = FAST ? a.unit_exp - sh : SC_ONE;   // scale of the weights
                         // the conversion to a byte rounds to nearest: half a
                         // unit less its own step below makes it a floor
                         const float bias = FAST ? 0.5f - 0.5f * inv : 0.f;
@@ -434,20 +522,21 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
                                 const uint32_t im = s_img[k * KP + slot];
                                 const uint32_t ph = s_phi[k * KP + slot] | s_pc[k];
                                 if (FAST) {
-                                    if (a.code_img == 1 && a.code_phi == 9) {
+                                    if (a.code_img == CODE_ONE && a.code_phi == (CODE_ONE | 0x8888u)) {
+                                        // weights 1 and -1: Phi sets the sign (Phi is in Img)
+                                        spread_one(im, B[n][0][ks]);
 #pragma unroll
-                                        for (int j = 0; j < 4; ++j)
-                                            B[n][0][ks][j] = ((im >> j) & NIB) | (((ph >> j) & NIB) << 3);
+                                        for (int j = 0; j < 4; ++j) B[n][0][ks][j] |= ((ph >> j) & NIB) << 3;
                                     } else {
-                                        const uint32_t ao = im & ~ph;
+                                        uint32_t x[4];
+                                        spread_slot(im & ~ph, a.code_img, B[n][0][ks]);
+                                        spread_slot(ph, a.code_phi, x);
 #pragma unroll
-                                        for (int j = 0; j < 4; ++j)
-                                            B[n][0][ks][j] = ((ao >> j) & NIB) * (uint32_t)a.code_img |
-                                                             ((ph >> j) & NIB) * (uint32_t)a.code_phi;
+                                        for (int j = 0; j < 4; ++j) B[n][0][ks][j] |= x[j];
                                     }
                                 } else {
-                                    spread(ph, B[n][0][ks]);
-                                    spread(im, B[n][1][ks]);
+                                    spread_one(ph, B[n][0][ks]);
+                                    spread_one(im, B[n][1][ks]);
                                 }
                                 if (LAB) {
                                     const uint32_t f0 = s_phi[(W + k) * KP + slot] | s_pc[W + k];
@@ -455,125 +544,144 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
 #pragma unroll
                                     for (int l = 0; l < 4; ++l) {
                                         const uint32_t m = ph & ((l & 1) ? f0 : ~f0) & ((l & 2) ? f1 : ~f1);
-#pragma unroll
-                                        for (int j = 0; j < 4; ++j)
-                                            B[n][NOP - 4 + l][ks][j] =
-                                                FAST ? ((m >> j) & NIB) * (uint32_t)a.code_same : ((m >> j) & NIB);
+                                        if (FAST) spread_slot(m, a.code_same, B[n][NOP - 4 + l][ks]);
+                                        else spread_one(m, B[n][NOP - 4 + l][ks]);
                                     }
                                 }
                             }
                         }
-                        // (opaque, so that the tiles' bounds are compared where
-                        // they are needed and not kept for the whole pair)
                         // (unit matrix of the strike-out step: row `col` of an even tile)
                         uint32_t e_lo[4];
-                        spread(1u << col, e_lo);
+                        spread_row(1u << col, e_lo);
+                        // (opaque, so that the tiles' bounds are compared where
+                        // they are needed and not kept for the whole pair)
                         int n2v = __builtin_amdgcn_readfirstlane(n2), qv = q;
                         asm volatile("" : "+s"(n2v), "+v"(qv));
+                        constexpr int TG = 8 / UW;           // tiles of a 128-vertex group
+                        constexpr int TP = TG >= 4 && W == 16 ? 4 : (TG > 1 ? 2 : 1);   // tiles in flight
 #pragma unroll
                         for (int g = 0; g < (2 * WU + 7) / 8; ++g) {
                             uint32_t bd[NT][4];
 #pragma unroll
                             for (int n = 0; n < NT; ++n)
-                                spread(s_img[(4 * g + qv) * KP + (sw * NT + n) * 16 + col], bd[n]);
+                                spread_one(s_img[(4 * g + qv) * KP + (sw * NT + n) * 16 + col], bd[n]);
 #pragma unroll
-                            for (int kk = 0; kk < 8 / UW; ++kk) {
-                                const int k = g * (8 / UW) + kk;   // this wave's k-th target tile
-                                if (k >= NTL) continue;
-                                const int tile = k * UW + uw;
-                                __builtin_amdgcn_sched_barrier(0);   // one tile's operands at a time
-                                if (16 * tile >= n2v) {
+                            for (int kk = 0; kk < TG; kk += TP) {
+                                const int k0 = g * TG + kk;   // this wave's tiles k0 .. k0 + TP - 1
+                                if (k0 >= NTL) continue;
+                                // a few tiles' operands at a time
+                                __builtin_amdgcn_sched_barrier(0);
+                                if (16 * (k0 * UW + uw) >= n2v) {
 #pragma unroll
-                                    for (int n = 0; n < NT; ++n) cand[n][k] = DEAD;
+                                    for (int h = 0; h < TP; ++h)
+#pragma unroll
+                                        for (int n = 0; n < NT; ++n)
+                                            if (k0 + h < NTL) cand[n][k0 + h] = DEAD;
                                     continue;
                                 }
-                                uint32_t A[KST][4], Ad[4];
-                                uint32_t rw[KST], rp0[KST], rp1[KST];
+                                v4f dd[TP][NT], kp[TP][NT], ii[TP][NT], same[TP][NT];
+                                uint32_t rw[TP][KST], rp0[TP][KST], rp1[TP][KST];
+                                v4f lcv[TP];
 #pragma unroll
-                                for (int ks = 0; ks < KST; ++ks) {
-                                    const int at = (4 * ks + qv) * URS + 16 * tile + col;
-                                    rw[ks] = s_rows[at];
-                                    spread(rw[ks], A[ks]);
-                                    if (LAB) {
-                                        rp0[ks] = s_rows[W * URS + at];
-                                        rp1[ks] = s_rows[2 * W * URS + at];
+                                for (int h = 0; h < TP; ++h) {
+                                    if (k0 + h >= NTL) continue;
+                                    const int tile = (k0 + h) * UW + uw;
+#pragma unroll
+                                    for (int ks = 0; ks < KST; ++ks) {
+                                        const int at = (4 * ks + qv) * URS + 16 * tile + col;
+                                        rw[h][ks] = s_rows[at];
+                                        if (LAB) {
+                                            rp0[h][ks] = s_rows[W * URS + at];
+                                            rp1[h][ks] = s_rows[2 * W * URS + at];
+                                        }
                                     }
+                                    lcv[h] = *reinterpret_cast<const v4f *>(&s_lc[16 * tile + 4 * qv]);
                                 }
-                                const bool here = qv == ((tile >> 1) & 3);
 #pragma unroll
-                                for (int j = 0; j < 4; ++j) Ad[j] = here ? ((tile & 1) ? e_lo[j] << 16 : e_lo[j]) : 0u;
-                                const v4f lcv = *reinterpret_cast<const v4f *>(&s_lc[16 * tile + 4 * qv]);
-                                if (FAST) {
-                                    v4f acc[NT], dd[NT];
+                                for (int h = 0; h < TP; ++h) {
+                                    if (k0 + h >= NTL) continue;
+                                    const int tile = (k0 + h) * UW + uw;
+                                    uint32_t Ad[4];
+                                    const bool here = qv == ((tile >> 1) & 3);
+#pragma unroll
+                                    for (int j = 0; j < 4; ++j) Ad[j] = here ? ((tile & 1) ? e_lo[j] << 16 : e_lo[j]) : 0u;
 #pragma unroll
                                     for (int n = 0; n < NT; ++n) {
+                                        const v4f z = v4f{0.f, 0.f, 0.f, 0.f};
+                                        dd[h][n] = z;
+                                        if (FAST) {
 #pragma unroll
-                                        for (int r = 0; r < 4; ++r) dd[n][r] = __builtin_fmaf(lcv[r], inv, basef[n]);
-                                        dd[n] = mfma_fp4(Ad, bd[n], dd[n], SC_BIG);
-                                        acc[n] = v4f{0.f, 0.f, 0.f, 0.f};
+                                            for (int r = 0; r < 4; ++r) dd[h][n][r] = __builtin_fmaf(lcv[h][r], inv, basef[n]);
+                                        }
+                                        // FAST: dd is the child; else the mark of a used vertex, and
+                                        // the counts |Phi & N2(u)|, |Img & N2(u)|, same apart
+                                        dd[h][n] = mfma_fp4(Ad, bd[n], dd[h][n], SC_BIG, SC_ONE);
+                                        kp[h][n] = ii[h][n] = same[h][n] = z;
                                     }
+                                }
 #pragma unroll
-                                    for (int ks = 0; ks < KST; ++ks)
+                                for (int ks = 0; ks < KST; ++ks)
 #pragma unroll
-                                        for (int n = 0; n < NT; ++n) acc[n] = mfma_fp4(A[ks], B[n][0][ks], acc[n], SC_ONE);
-                                    if (LAB) {
+                                    for (int h = 0; h < TP; ++h) {
+                                        if (k0 + h >= NTL) continue;
+                                        uint32_t A[4];
+                                        spread_row(rw[h][ks], A);
 #pragma unroll
-                                        for (int l = 0; l < 4; ++l) {
-                                            if (l >= 2 && P < 2) continue;   // one plane: two codes
+                                        for (int n = 0; n < NT; ++n) {
+                                            if (FAST) {
+                                                dd[h][n] = mfma_fp4(A, B[n][0][ks], dd[h][n], SC_ONE, sc);
+                                            } else {
+                                                kp[h][n] = mfma_fp4(A, B[n][0][ks], kp[h][n], SC_ONE, SC_ONE);
+                                                ii[h][n] = mfma_fp4(A, B[n][1][ks], ii[h][n], SC_ONE, SC_ONE);
+                                            }
+                                        }
+                                        if (LAB) {
 #pragma unroll
-                                            for (int ks = 0; ks < KST; ++ks) {
-                                                uint32_t Al[4];
-                                                spread(rw[ks] & ((l & 1) ? rp0[ks] : ~rp0[ks]) & ((l & 2) ? rp1[ks] : ~rp1[ks]), Al);
+                                            for (int l = 0; l < 4; ++l) {
+                                                if (FAST && l >= 2 && P < 2) continue;   // one plane: two codes
+                                                spread_row(rw[h][ks] & ((l & 1) ? rp0[h][ks] : ~rp0[h][ks]) &
+                                                               ((l & 2) ? rp1[h][ks] : ~rp1[h][ks]), A);
 #pragma unroll
-                                                for (int n = 0; n < NT; ++n)
-                                                    acc[n] = mfma_fp4(Al, B[n][NOP - 4 + l][ks], acc[n], SC_ONE);
+                                                for (int n = 0; n < NT; ++n) {
+                                                    if (FAST) dd[h][n] = mfma_fp4(A, B[n][NOP - 4 + l][ks], dd[h][n], SC_ONE, sc);
+                                                    else same[h][n] = mfma_fp4(A, B[n][NOP - 4 + l][ks], same[h][n], SC_ONE, SC_ONE);
+                                                }
                                             }
                                         }
                                     }
 #pragma unroll
+                                for (int h = 0; h < TP; ++h)
+#pragma unroll
                                     for (int n = 0; n < NT; ++n) {
-                                        float y[4];
+                                        if (k0 + h >= NTL) continue;
                                         uint32_t w = 0u;
+                                        if (FAST) {
+                                            const v4f y = dd[h][n];
 #pragma unroll
-                                        for (int r = 0; r < 4; ++r) y[r] = __builtin_fmaf(acc[n][r], gi, dd[n][r]);
+                                            for (int r = 0; r < 4; ++r) w = __builtin_amdgcn_cvt_pk_u8_f32(fminf(y[r], (float)XCAP), r, w);
+                                            yminf = fminf(yminf, fminf(fminf(y[0], y[1]), fminf(y[2], y[3])));
+                                        } else {
+                                            const bool dead = (sw * NT + n) * 16 + col >= nb;
 #pragma unroll
-                                        for (int r = 0; r < 4; ++r) w = __builtin_amdgcn_cvt_pk_u8_f32(fminf(y[r], (float)XCAP), r, w);
-                                        cand[n][k] = w;
-                                        yminf = fminf(yminf, fminf(fminf(y[0], y[1]), fminf(y[2], y[3])));
+                                            for (int r = 0; r < 4; ++r) {
+                                                const int kept = (int)kp[h][n][r];
+                                                int y = basei[n] + __float_as_int(lcv[h][r]) + c.eins * ((int)ii[h][n][r] - kept) - c.edel * kept;
+                                                if (LAB) y += c.esub * (kept - (int)same[h][n][r]);
+                                                y = (dead || dd[h][n][r] > 0.5f) ? 0x7fffffff : y;
+                                                ymini = min(ymini, y);
+                                                w |= (uint32_t)min(max(y >> sh, 0), XCAP) << (8 * r);
+                                            }
+                                        }
+                                        cand[n][k0 + h] = w;
                                     }
-                                } else {
+                                // alternate the pipes' instructions: 31.0 -> 29.7 thousand
+                                // cycles a level at 500 vertices, K = 256 (no gain on
+                                // shorter chains)
+                                if (FAST && TP == 4) {
 #pragma unroll
-                                    for (int n = 0; n < NT; ++n) {
-                                        v4f z = v4f{0.f, 0.f, 0.f, 0.f};
-                                        const v4f dd = mfma_fp4(Ad, bd[n], z, SC_BIG);
-                                        v4f kp = z, ii = z, sm = z;
-#pragma unroll
-                                        for (int ks = 0; ks < KST; ++ks) {
-                                            kp = mfma_fp4(A[ks], B[n][0][ks], kp, SC_ONE);
-                                            ii = mfma_fp4(A[ks], B[n][1][ks], ii, SC_ONE);
-                                        }
-                                        if (LAB) {
-#pragma unroll
-                                            for (int l = 0; l < 4; ++l)
-#pragma unroll
-                                                for (int ks = 0; ks < KST; ++ks) {
-                                                    uint32_t Al[4];
-                                                    spread(rw[ks] & ((l & 1) ? rp0[ks] : ~rp0[ks]) & ((l & 2) ? rp1[ks] : ~rp1[ks]), Al);
-                                                    sm = mfma_fp4(Al, B[n][NOP - 4 + l][ks], sm, SC_ONE);
-                                                }
-                                        }
-                                        uint32_t w = 0u;
-                                        const bool dead = (sw * NT + n) * 16 + col >= nb;
-#pragma unroll
-                                        for (int r = 0; r < 4; ++r) {
-                                            const int kept = (int)kp[r];
-                                            int y = basei[n] + __float_as_int(lcv[r]) + c.eins * ((int)ii[r] - kept) - c.edel * kept;
-                                            if (LAB) y += c.esub * (kept - (int)sm[r]);
-                                            y = (dead || dd[r] > 0.5f) ? 0x7fffffff : y;
-                                            ymini = min(ymini, y);
-                                            w |= (uint32_t)min(max(y >> sh, 0), XCAP) << (8 * r);
-                                        }
-                                        cand[n][k] = w;
+                                    for (int z = 0; z < TP * NT * (KST * (LAB ? 5 : 1) + 1); ++z) {
+                                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                                        __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);
                                     }
                                 }
                             }
@@ -675,14 +783,23 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
                     for (int n = 0; n < NT; ++n) {
                         const int slot = (sw * NT + n) * 16 + col;
 #pragma unroll
-                        for (int k = 0; k < NCAND; ++k) {
-                            const uint32_t fle = (Cle - cand[n][k]) & HI;
-                            if (fle) {
-                                const uint32_t flt = (Clt - cand[n][k]) & HI;
-                                const int tile = k * UW + uw;
-                                const int row = k < NTL ? (tile >> 1) * KP + slot : WU * KP + slot;
-                                const int shf = k < NTL ? 16 * (tile & 1) + 4 * q : 0;
-                                atomicOr(&s_le[row], (__builtin_amdgcn_udot4(fle, 0x08040201u, 0u, false) >> 7) << shf);
+                        for (int k4 = 0; k4 < NCAND; k4 += 4) {
+                            // most words hold no survivor: one test for four
+                            uint32_t f[4], any = 0u;
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) {
+                                f[k] = k4 + k < NCAND ? (Cle - cand[n][k4 + k < NCAND ? k4 + k : 0]) & HI : 0u;
+                                any |= f[k];
+                            }
+                            if (!any) continue;
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) {
+                                if (k4 + k >= NCAND || !f[k]) continue;
+                                const uint32_t flt = (Clt - cand[n][k4 + k]) & HI;
+                                const int tile = (k4 + k) * UW + uw;
+                                const int row = k4 + k < NTL ? (tile >> 1) * KP + slot : WU * KP + slot;
+                                const int shf = k4 + k < NTL ? 16 * (tile & 1) + 4 * q : 0;
+                                atomicOr(&s_le[row], (__builtin_amdgcn_udot4(f[k], 0x08040201u, 0u, false) >> 7) << shf);
                                 if (flt)
                                     atomicOr(&s_lt[row], (__builtin_amdgcn_udot4(flt, 0x08040201u, 0u, false) >> 7) << shf);
                             }
@@ -691,60 +808,49 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
                 }
                 __syncthreads();
 
-                // ---------------- emission in generation order: slot, vertex, the deletion last
-                // (the first KS / 64 waves, a slot per lane)
-                int lt = 0, eq = 0, LT = 0, EQ = 0;
-                if (t < (KS < 64 ? 64 : KS)) {
-                    const int s = t;
-                    if (s < KS) {
+                // ---------------- emission in generation order: slot, vertex, the
+                // deletion last; a thread takes CW words of its slot's masks.
+                // One scan of (children below T, ties at T), the ties capped at K
+                uint32_t ml[CW], me[CW];
+                int lt = 0, eq = 0;
 #pragma unroll
-                        for (int k = 0; k <= WU; ++k) {
-                            lt += __popc(s_lt[k * KP + s]);
-                            eq += __popc(s_le[k * KP + s]);
-                        }
-                    }
-                    eq -= lt;
-                    LT = wave_excl_scan(lt);
-                    EQ = wave_excl_scan(eq);
-                    if (KS > 64 && lane == 63) {
-                        s_red[0][wid] = (uint32_t)(LT + lt);
-                        s_red[1][wid] = (uint32_t)(EQ + eq);
-                    }
+                for (int k = 0; k < CW; ++k) {
+                    const int w = part * CW + k;
+                    const uint32_t m = w <= WU ? s_lt[w * KP + us] : 0u;
+                    ml[k] = m;
+                    me[k] = (w <= WU ? s_le[w * KP + us] : 0u) & ~m;
+                    lt += __popc(ml[k]);
+                    eq += __popc(me[k]);
                 }
-                int allt = 0;
-                if (KS > 64) {
-                    __syncthreads();
-                    if (t < KS) {
+                const uint32_t both = (uint32_t)lt | ((uint32_t)min(eq, K) << 11);
+                uint32_t pre = (uint32_t)wave_excl_scan((int)both);
+                if (lane == 63) s_red[0][wid] = pre + both;
+                __syncthreads();
+                uint32_t all = 0u;
 #pragma unroll
-                        for (int k = 0; k < KS / 64; ++k) {
-                            const int x = (int)s_red[0][k], y = (int)s_red[1][k];
-                            LT += k < wid ? x : 0;
-                            EQ += k < wid ? y : 0;
-                            allt += x;
-                        }
-                    }
-                } else if (t < 64) {
-                    allt = __builtin_amdgcn_readlane(LT + lt, 63);
+                for (int k = 0; k < NWV; ++k) {
+                    const uint32_t x = s_red[0][k];
+                    pre += k < wid ? x : 0u;
+                    all += x;
                 }
                 nb_new = min(V, K);
-                if (t < KS && lt + eq > 0) {
-                    quota = nb_new - allt;          // ties at T that survive
-                    const int eqb = min(EQ, quota); // ... of the slots before
+                if (lt + eq > 0) {
+                    quota = nb_new - (int)(all & 2047u);            // ties at T that survive
+                    const int eqb = min((int)(pre >> 11), quota);   // ... of the threads before
                     int keq = min(quota - eqb, eq);
-                    int pos = LT + eqb;
-#pragma unroll 1
-                    for (int k = 0; k <= WU; ++k) {
-                        uint32_t m = s_le[k * KP + t];
-                        if (!m) continue;
-                        const uint32_t ml = s_lt[k * KP + t];
+                    int pos = (int)(pre & 2047u) + eqb;
+#pragma unroll
+                    for (int k = 0; k < CW; ++k) {
+                        uint32_t m = keq > 0 ? ml[k] | me[k] : ml[k];
                         while (m) {
                             const uint32_t bit = m & (0u - m);
                             m ^= bit;
-                            if (!(ml & bit)) {
+                            if (me[k] & bit) {
                                 if (keq == 0) continue;
                                 --keq;
                             }
-                            s_sel[pos++] = (t << 10) | (k < WU ? 32 * k + (int)__builtin_ctz(bit) : DELU);
+                            const int w = part * CW + k;
+                            s_sel[pos++] = (us << 10) | (w < WU ? 32 * w + (int)__builtin_ctz(bit) : DELU);
                         }
                     }
                 }
@@ -858,6 +964,7 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
                         s_lt[w * KP + us] = 0u;
                     }
                     if (t < NA * W) s_pc[t] = 0u;
+                    if (t < ND * NA * W1) s_r1[((i + 1) & 1) * (ND * NA * W1) + t] = rown;
                     if (t == 0) {
                         s_neq = 0;
                         s_sumV[par ^ 1] = 0;

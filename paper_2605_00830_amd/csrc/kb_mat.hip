@@ -34,35 +34,9 @@ MatConfig mat_config(const BlockShape &s) {
 
 int slots_of(const MatConfig &m) { return 16 * m.NT * m.SW; }
 
-MatLds lds_for(const BlockShape &s, const MatConfig &m) {
-    MatLds L{};
-    const int W = m.W, KS = slots_of(m), NA = s.PL > 0 ? 3 : 1, WU = s.directed ? W / 2 : W;
-    const int KP = KS % 64 == 0 ? KS + 16 : (KS == 32 ? 48 : KS);
-    const int n1 = std::max(s.nmax1, 1);
-    int off = 0;
-    auto take = [&](int bytes) {
-        const int o = off;
-        off += (bytes + 15) & ~15;
-        return o;
-    };
-    const int URS = 32 * WU + 16;
-    L.rows = take(NA * W * URS * 4);
-    L.lc = take(URS * 4);
-    L.img = take(W * KP * 4);
-    L.phi = take(NA * W * KP * 4);
-    L.le = take((WU + 1) * KP * 4);
-    L.lt = take((WU + 1) * KP * 4);
-    L.anc = take((n1 + BL - 1) / BL * KS * 2);
-    L.cur = take(BL * KS * 2);
-    L.com = take(n1 * 2);
-    L.nbr = take(n1 * (s.directed ? 2 : 1) * 2);
-    L.nbc = take(n1 * (s.directed ? 2 : 1));
-    L.pc = take(NA * W * 4);
-    L.ped = take(KS * 4);
-    L.nsub = take(KS * 4);
-    L.sel = take(KS * 4);
-    L.bytes = off;
-    return L;
+int lds_bytes(const BlockShape &s, const MatConfig &m) {
+    const int KS = slots_of(m), blocks = (std::max(s.nmax1, 1) + BL - 1) / BL;
+    return mat_lds(m.W, KS, s.PL > 0 ? 3 : 1, s.directed ? 2 : 1).anc + blocks * KS * 2;
 }
 
 constexpr int kMatLdsBytes = 158 * 1024;
@@ -72,27 +46,17 @@ const void *mat_kernel(const BlockShape &s, const MatConfig &m, bool fast) {
     return s.directed ? mat_kernel_dir(m, fast) : mat_kernel_plain(m, fast);
 }
 
-// fp4 code of the integer m (0.5 m in E2M1), or -1.
-int fp4_code(int64_t m) {
-    const int sign = m < 0 ? 8 : 0;
-    switch (m < 0 ? -m : m) {
-        case 0: return 0;
-        case 1: return sign | 1;
-        case 2: return sign | 2;
-        case 3: return sign | 3;
-        case 4: return sign | 4;
-        case 6: return sign | 5;
-        case 8: return sign | 6;
-        case 12: return sign | 7;
-        default: return -1;
-    }
+// Nibbles of weight m (-3 .. 3) for spread_slot: 2 m, m, m / 2 and 2 m in fp4.
+uint32_t slot_code(int64_t m) {
+    static const uint32_t mag[4] = {0x0000u, CODE_ONE, 0x6246u, 0x7357u};
+    return mag[m < 0 ? -m : m] | (m < 0 ? 0x8888u : 0u);
 }
 
 }  // namespace
 
 bool mat_supported(const BlockShape &s) {
     const MatConfig m = mat_config(s);
-    return m.W != 0 && lds_for(s, m).bytes <= kMatLdsBytes && mat_kernel(s, m, true) != nullptr;
+    return m.W != 0 && lds_bytes(s, m) <= kMatLdsBytes && mat_kernel(s, m, true) != nullptr;
 }
 
 size_t mat_workspace_bytes(const BlockShape &s) {
@@ -102,12 +66,10 @@ size_t mat_workspace_bytes(const BlockShape &s) {
 
 hipError_t mat_max_resident(const BlockShape &s, int *blocks_per_cu) {
     const MatConfig m = mat_config(s);
-    const int threads = 64 * m.SW * m.UW, lds = lds_for(s, m).bytes;
-    int f = 0, g = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&f, mat_kernel(s, m, true), threads, lds);
-    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&g, mat_kernel(s, m, false), threads, lds);
-    *blocks_per_cu = std::min(f, g);
-    return e;
+    // (the grid is sized for the matrix form of the costs; the other needs
+    // more registers, and a grid beyond what is resident at once only queues)
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, mat_kernel(s, m, true), 64 * m.SW * m.UW,
+                                                        lds_bytes(s, m));
 }
 
 hipError_t launch_mat(const BlockShape &s, const DbView &src, const DbView &dst, const WorkItem *work, int nwork,
@@ -126,7 +88,6 @@ hipError_t launch_mat(const BlockShape &s, const DbView &src, const DbView &dst,
     a.last_complete = last_complete;
     a.ws = static_cast<char *>(workspace);
     a.ws_stride = ws_stride;
-    a.L = lds_for(s, m);
     a.out = out;
     // the largest PED of any pair of these orders, and whether the costs fit
     // the matrix operands
@@ -136,25 +97,20 @@ hipError_t launch_mat(const BlockShape &s, const DbView &src, const DbView &dst,
     a.pedbound = (uint32_t)std::min<int64_t>(bound, 0x7fffffff);
     const bool lab = s.PL > 0;
     const int64_t ci = c.eins, cp = lab ? (int64_t)c.esub - c.edel : -(int64_t)c.edel, cs = lab ? -(int64_t)c.esub : 0;
-    int64_t g = 0;
-    for (int64_t x : {ci, cp, cs}) {
-        x = x < 0 ? -x : x;
-        while (x) {
-            const int64_t r = g % x;
-            g = x;
-            x = r;
-        }
+    bool fast = bound < kFastBound;
+    int e = 0;   // unit 2^e: the largest that divides the three
+    while (e < 21 && (((ci | cp | cs) >> e) & 1) == 0) ++e;
+    for (int64_t x : {ci, cp, cs}) fast = fast && x % ((int64_t)1 << e) == 0 && x / ((int64_t)1 << e) >= -3 && x / ((int64_t)1 << e) <= 3;
+    if (fast) {
+        a.code_img = slot_code(ci / ((int64_t)1 << e));
+        a.code_phi = slot_code(cp / ((int64_t)1 << e));
+        a.code_same = slot_code(cs / ((int64_t)1 << e));
+        a.unit_exp = SC_ONE + e;
     }
-    if (g == 0) g = 1;
-    a.code_img = fp4_code(ci / g);
-    a.code_phi = fp4_code(cp / g);
-    a.code_same = fp4_code(cs / g);
-    a.unit = (float)g;
-    const bool fast = bound < kFastBound && a.code_img >= 0 && a.code_phi >= 0 && a.code_same >= 0;
     const void *k = mat_kernel(s, m, fast);
     if (!k) return hipErrorInvalidValue;
     void *args[] = {&a};
-    return hipLaunchKernel(k, dim3(grid), dim3(64 * m.SW * m.UW), args, (size_t)a.L.bytes, stream);
+    return hipLaunchKernel(k, dim3(grid), dim3(64 * m.SW * m.UW), args, (size_t)lds_bytes(s, m), stream);
 }
 
 }  // namespace gedk
