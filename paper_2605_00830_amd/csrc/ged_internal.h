@@ -88,6 +88,15 @@ hipError_t launch_wide(const DbView &src, const DbView &dst, const GraphRec &g1,
                        int last_complete, void *ws, size_t ws_bytes, int32_t *dist, int32_t *map, int64_t *cand,
                        int cus, hipStream_t stream);
 
+// The same for targets of up to 32 vertices when no PED of the search reaches
+// kWide1Bound (kb_wide1.hip); launch_wide calls it wherever that holds.
+constexpr int kWide1MaxN2 = 32;
+constexpr int kWide1Bound = 4096;
+size_t wide1_workspace_bytes(int n1, int planes, int K);
+hipError_t launch_wide1(const DbView &src, const DbView &dst, const GraphRec &g1, const GraphRec &g2, Costs c, int K,
+                        int last_complete, uint32_t pedmax, void *ws, size_t ws_bytes, int32_t *dist, int32_t *map,
+                        int64_t *cand, int cus, hipStream_t stream);
+
 // Wavefront family that fits a pair: 1 (n1, n2 <= 32 and K <= 64), 2 (else
 // n1, n2 <= 64 and K <= 128), 3 (n2 <= 64, 64 < n1 <= 128 and K <= 128: the
 // two-word kernel with a 128-vertex mapping), 0 none (K > 128 or a larger

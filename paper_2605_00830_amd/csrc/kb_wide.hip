@@ -927,13 +927,22 @@ hipError_t launch_pl(int PL, const WideCtx &c, bool refine_possible, bool last_c
 }  // namespace
 
 size_t wide_workspace_bytes(int n1, int n2, int w2, int planes, int K) {
-    return layout(n1, n2, w2, planes, slot_stride(K)).total;
+    const size_t full = layout(n1, n2, w2, planes, slot_stride(K)).total;
+    return n2 <= kWide1MaxN2 ? std::max(full, wide1_workspace_bytes(n1, planes, K)) : full;
 }
 
 hipError_t launch_wide(const DbView &src, const DbView &dst, const GraphRec &g1, const GraphRec &g2, Costs costs,
                        int K, int last_complete, void *ws, size_t ws_bytes, int32_t *dist, int32_t *map,
                        int64_t *cand, int cus, hipStream_t stream) {
     const int planes = dst.planes;
+    // vertex and edge operations of any search of the pair
+    const int64_t vmax = std::max({(int64_t)costs.vsub, (int64_t)costs.vdel, (int64_t)costs.vins});
+    const int64_t emax = std::max({(int64_t)costs.esub, (int64_t)costs.edel, (int64_t)costs.eins});
+    const uint64_t pedmax =
+        (uint64_t)(vmax * ((int64_t)g1.n + g2.n) + emax * ((int64_t)g1.m + g2.m));
+    if (g2.n <= kWide1MaxN2 && pedmax < (uint64_t)kWide1Bound)
+        return launch_wide1(src, dst, g1, g2, costs, K, last_complete, (uint32_t)pedmax, ws, ws_bytes, dist, map, cand,
+                            cus, stream);
     const int PL = planes == 0 ? 0 : (planes <= 2 ? 2 : 4);
     int W = 1;
     while (W < g2.w) W <<= 1;
@@ -978,9 +987,7 @@ hipError_t launch_wide(const DbView &src, const DbView &dst, const GraphRec &g1,
     c.out_cand = cand;
     // no PED of the search exceeds pedmax, so the expansion histogram needs a
     // shift (and refinement) only if pedmax does not fit its bins
-    const int64_t vmax = std::max({(int64_t)costs.vsub, (int64_t)costs.vdel, (int64_t)costs.vins});
-    const int64_t emax = std::max({(int64_t)costs.esub, (int64_t)costs.edel, (int64_t)costs.eins});
-    c.pedmax = (uint64_t)(vmax * (int64_t)g1.n + emax * ((int64_t)g1.m + g2.m));
+    c.pedmax = pedmax;
     const bool refine_possible = c.pedmax >= (uint64_t)HB;
     const bool lc = last_complete != 0;
     switch (W) {
