@@ -97,6 +97,14 @@ hipError_t launch_wide1(const DbView &src, const DbView &dst, const GraphRec &g1
                         int last_complete, uint32_t pedmax, void *ws, size_t ws_bytes, int32_t *dist, int32_t *map,
                         int64_t *cand, int cus, hipStream_t stream);
 
+// ... and for larger targets without edge labels on the matrix cores
+// (kb_widem.hip), wherever widem_takes the costs.
+size_t widem_workspace_bytes(int n1, int w2, int K);
+bool widem_takes(const GraphRec &g1, const GraphRec &g2, int planes, Costs c, uint64_t pedmax);
+hipError_t launch_widem(const DbView &src, const DbView &dst, const GraphRec &g1, const GraphRec &g2, Costs c, int K,
+                        int last_complete, uint32_t pedmax, void *ws, size_t ws_bytes, int32_t *dist, int32_t *map,
+                        int64_t *cand, hipStream_t stream);
+
 // Wavefront family that fits a pair: 1 (n1, n2 <= 32 and K <= 64), 2 (else
 // n1, n2 <= 64 and K <= 128), 3 (n2 <= 64, 64 < n1 <= 128 and K <= 128: the
 // two-word kernel with a 128-vertex mapping), 0 none (K > 128 or a larger

@@ -1025,6 +1025,15 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
     }
 }
 
+// The slot operand's nibbles for these costs (plain: Img \ Phi and Phi; with
+// edge labels also Phi_c): false if they are not small multiples of a power of
+// two.
+struct SlotCodes {
+    uint32_t img = 0, phi = 0, same = 0;
+    int unit_exp = SC_ONE;
+};
+bool slot_codes(const Costs &c, bool labels, SlotCodes *out);
+
 struct MatConfig {
     int W = 0, NT = 0, SW = 0, UW = 0;   // W == 0: no instantiation
 };

@@ -11,6 +11,25 @@ const void *mat_kernel_plain(const MatConfig &m, bool fast) {
     return fast ? mat_select<false, false, true>(m) : mat_select<false, false, false>(m);
 }
 
+bool slot_codes(const Costs &c, bool labels, SlotCodes *out) {
+    // nibbles of weight m (0 .. 3) for spread_slot: 2 m, m, m / 2 and 2 m in fp4
+    static const uint32_t mag[4] = {0x0000u, CODE_ONE, 0x6246u, 0x7357u};
+    const int64_t w[3] = {c.eins, labels ? (int64_t)c.esub - c.edel : -(int64_t)c.edel, labels ? -(int64_t)c.esub : 0};
+    int e = 0;   // unit 2^e: the largest that divides the three
+    while (e < 21 && (((w[0] | w[1] | w[2]) >> e) & 1) == 0) ++e;
+    uint32_t code[3];
+    for (int k = 0; k < 3; ++k) {
+        const int64_t unit = (int64_t)1 << e, m = w[k] / unit;
+        if (w[k] % unit != 0 || m < -3 || m > 3) return false;
+        code[k] = mag[m < 0 ? -m : m] | (m < 0 ? 0x8888u : 0u);
+    }
+    out->img = code[0];
+    out->phi = code[1];
+    out->same = code[2];
+    out->unit_exp = SC_ONE + e;
+    return true;
+}
+
 }  // namespace mat
 
 using namespace mat;
@@ -44,12 +63,6 @@ constexpr int kMatLdsBytes = 158 * 1024;
 const void *mat_kernel(const BlockShape &s, const MatConfig &m, bool fast) {
     if (s.PL > 0) return s.directed ? mat_kernel_dir_lab(m, fast) : mat_kernel_lab(m, fast);
     return s.directed ? mat_kernel_dir(m, fast) : mat_kernel_plain(m, fast);
-}
-
-// Nibbles of weight m (-3 .. 3) for spread_slot: 2 m, m, m / 2 and 2 m in fp4.
-uint32_t slot_code(int64_t m) {
-    static const uint32_t mag[4] = {0x0000u, CODE_ONE, 0x6246u, 0x7357u};
-    return mag[m < 0 ? -m : m] | (m < 0 ? 0x8888u : 0u);
 }
 
 }  // namespace
@@ -95,18 +108,12 @@ hipError_t launch_mat(const BlockShape &s, const DbView &src, const DbView &dst,
     const int64_t e1 = (int64_t)s.nmax1 * (s.nmax1 - 1), e2 = (int64_t)s.nmax2 * (s.nmax2 - 1);
     const int64_t bound = vmax * ((int64_t)s.nmax1 + s.nmax2) + emax * (s.directed ? e1 + e2 : (e1 + e2) / 2);
     a.pedbound = (uint32_t)std::min<int64_t>(bound, 0x7fffffff);
-    const bool lab = s.PL > 0;
-    const int64_t ci = c.eins, cp = lab ? (int64_t)c.esub - c.edel : -(int64_t)c.edel, cs = lab ? -(int64_t)c.esub : 0;
-    bool fast = bound < kFastBound;
-    int e = 0;   // unit 2^e: the largest that divides the three
-    while (e < 21 && (((ci | cp | cs) >> e) & 1) == 0) ++e;
-    for (int64_t x : {ci, cp, cs}) fast = fast && x % ((int64_t)1 << e) == 0 && x / ((int64_t)1 << e) >= -3 && x / ((int64_t)1 << e) <= 3;
-    if (fast) {
-        a.code_img = slot_code(ci / ((int64_t)1 << e));
-        a.code_phi = slot_code(cp / ((int64_t)1 << e));
-        a.code_same = slot_code(cs / ((int64_t)1 << e));
-        a.unit_exp = SC_ONE + e;
-    }
+    SlotCodes codes;
+    const bool fast = bound < kFastBound && slot_codes(c, s.PL > 0, &codes);
+    a.code_img = codes.img;
+    a.code_phi = codes.phi;
+    a.code_same = codes.same;
+    a.unit_exp = codes.unit_exp;
     const void *k = mat_kernel(s, m, fast);
     if (!k) return hipErrorInvalidValue;
     void *args[] = {&a};

@@ -928,7 +928,8 @@ hipError_t launch_pl(int PL, const WideCtx &c, bool refine_possible, bool last_c
 
 size_t wide_workspace_bytes(int n1, int n2, int w2, int planes, int K) {
     const size_t full = layout(n1, n2, w2, planes, slot_stride(K)).total;
-    return n2 <= kWide1MaxN2 ? std::max(full, wide1_workspace_bytes(n1, planes, K)) : full;
+    if (n2 <= kWide1MaxN2) return std::max(full, wide1_workspace_bytes(n1, planes, K));
+    return planes == 0 ? std::max(full, widem_workspace_bytes(n1, w2, K)) : full;
 }
 
 hipError_t launch_wide(const DbView &src, const DbView &dst, const GraphRec &g1, const GraphRec &g2, Costs costs,
@@ -943,6 +944,9 @@ hipError_t launch_wide(const DbView &src, const DbView &dst, const GraphRec &g1,
     if (g2.n <= kWide1MaxN2 && pedmax < (uint64_t)kWide1Bound)
         return launch_wide1(src, dst, g1, g2, costs, K, last_complete, (uint32_t)pedmax, ws, ws_bytes, dist, map, cand,
                             cus, stream);
+    if (widem_takes(g1, g2, planes, costs, pedmax))
+        return launch_widem(src, dst, g1, g2, costs, K, last_complete, (uint32_t)pedmax, ws, ws_bytes, dist, map, cand,
+                            stream);
     const int PL = planes == 0 ? 0 : (planes <= 2 ? 2 : 4);
     int W = 1;
     while (W < g2.w) W <<= 1;
