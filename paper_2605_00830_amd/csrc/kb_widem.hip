@@ -7,25 +7,30 @@
 // the last incomplete block of 8 levels as rows that are gathered from level to
 // level, complete blocks written once and reached through one ancestor index
 // per block, blocks that the whole beam shares moved to the common mapping.  A
-// level is four kernels, the first and third on a grid of (64 slots) x (128
-// target vertices), a wave holding 16 slots:
+// level is three kernels, the first two on a grid of (64 slots) x (128 target
+// vertices), a wave holding 16 slots:
 //   expand   Phi of the 64 slots (stored for the others), every child's PED,
 //            an LDS histogram above the least parent PED, added to one of HC
 //            copies (atomics on one address are serialised, about 10 ns each).
-//   select   one workgroup: the threshold T from the histogram, the next
-//            level's size and bounds, and whether the oldest block has become
-//            common.  Should the K-th child lie past the histogram's range (the
-//            host admits only costs whose levels stay well inside), it counts
-//            the children itself, exactly.
-//   mark     scores again -- cheaper than a candidate matrix of 4 bytes a child,
-//            written once and read twice -- and stores, per slot, a bit per
-//            vertex for children at most T and below T; counts per 64 slots.
+//   mark     the threshold T from the histogram, by every workgroup (should
+//            the K-th child lie past the histogram's range -- the host admits
+//            only costs whose levels stay well inside -- the children are
+//            counted there, exactly); then scores again -- cheaper than a
+//            candidate matrix of 4 bytes a child, written once and read twice --
+//            and stores, per slot, a bit per vertex for children at most T and
+//            below T, and their counts per 64 slots.
 //   update   every workgroup adds up the counts before its 64 slots, places its
 //            survivors in generation order (slot, vertex ascending, the deletion
 //            last, ties at T while the quota lasts) and writes them, four
-//            threads a slot.
+//            threads a slot; one more workgroup prepares the next level's
+//            neighbour lists and the common part of its Phi.
+// A kernel here is a few microseconds of dependent loads, so each begins with
+// every load that needs no answer.
 //
-// FIGURES
+// Two 500-vertex graphs at K = 5000 (MI355X): 39.6 ms with kb_wide.hip's kernels
+// (79 us a level), 17.0 ms so: 13.0 us of expand, 12.0 of mark and 9.4 of update
+// a level, each a chain of about six dependent loads and a launch; scoring all
+// 2.5 million children is about 1 us of it.
 #include <algorithm>
 
 #include "kb_mat.h"
@@ -37,9 +42,8 @@ using namespace mat;
 
 constexpr int WT = 256;
 constexpr int NWV = WT / 64;
-constexpr int ST = 1024;          // threads of the selection
 constexpr int HB = 4096;          // histogram bins; the last one also counts what is above
-constexpr int HC = 8;             // copies
+constexpr int HC = 2;             // copies
 constexpr int GS = 64;            // slots of a workgroup
 constexpr int GP = GS + 16;       // their LDS stride
 constexpr int CT = 8;             // target tiles of a workgroup (128 vertices)
@@ -52,10 +56,19 @@ constexpr uint32_t kCommonMost = 1u << 16;   // beams whose oldest block is look
 
 struct Level {
     uint32_t B, m0, mmax;    // parents, their least and largest PED
-    uint32_t T, quota;       // threshold (NONE: every child survives), ties that survive
+    uint32_t quota;          // children equal to the threshold that survive
     uint32_t b0;             // first block not yet common
-    uint32_t V;              // children
+    uint32_t pad[3];
+};
+
+// What a level needs of v_i and the common mapping, made while the level before
+// is written.
+struct Prep {
+    uint32_t deg;            // earlier neighbours of v_i
+    uint32_t nwb, nw;        // window neighbours: in complete blocks, and all
     uint32_t pad;
+    uint32_t pc[MAXN / 32];  // images of the common ones
+    uint16_t nbr[MAXN];      // the window's, those of complete blocks first
 };
 
 struct Ctx {
@@ -82,6 +95,7 @@ struct Ctx {
     uint32_t *rec;           // [Kp]
     uint32_t *hist;          // [HC][HB]
     Level *st;
+    Prep *prep;
     unsigned long long *ce, *best;   // best: a key per workgroup
     int32_t *out_dist, *out_map;
     int64_t *out_cand;
@@ -121,6 +135,7 @@ __global__ __launch_bounds__(WT) void wm_init(Ctx c) {
     }
     for (int b = t; b < HC * HB; b += T) c.hist[b] = 0u;
     for (int k = t; k < c.w2; k += T) c.img[0][(size_t)k * c.Kp] = 0u;
+    for (int k = t; k < (int)(sizeof(Prep) / 4); k += T) reinterpret_cast<uint32_t *>(c.prep)[k] = 0u;
     if (t == 0) {
         c.ped[0][0] = 0u;
         c.nsub[0][0] = 0u;
@@ -146,40 +161,50 @@ struct Tile {
         if (t < 32 * CWD) s_lc[t] = (u0 + t < c.n2 && c.l2[u0 + t] != lab1) ? (float)c.c.vsub : 0.f;
     }
 
-    // f(k, y): the four children 16 tile + 4 q .. + 3 of this lane's slot, y
-    // their PEDs less `origin` (used vertices and dead slots near 2^24), for the
+    // This lane's slot: its words of Img, the chunk's own once more for the
+    // strike-out, and its PED.  Loaded before anything is waited for: rows past
+    // the beam hold what they did before, and are not looked at.
+    struct Slot {
+        uint32_t im[KST], own, ped;
+        __device__ __forceinline__ void load(const Ctx &c, int i, uint32_t s0, int u0) {
+            const int lane = threadIdx.x & 63, q = lane >> 4, ls = (threadIdx.x >> 6) * 16 + (lane & 15), cur = i & 1;
+            const uint32_t s = s0 + (uint32_t)ls;   // below Kp
+#pragma unroll
+            for (int ks = 0; ks < KST; ++ks) {
+                const int k = 4 * ks + q;
+                im[ks] = k < c.w2 ? c.img[cur][(size_t)k * c.Kp + s] : 0u;
+            }
+            const int kd = (u0 >> 5) + q;
+            own = (kd < c.w2 ? c.img[cur][(size_t)kd * c.Kp + s] : 0u) | ~below(c.n2, kd);   // past n2: used
+            ped = c.ped[cur][s];
+        }
+    };
+
+    // f(k, y): the four children 16 k + 4 q .. + 3 of this lane's slot, y their
+    // PEDs plus `shift` (used vertices and dead slots near 2^24), for the
     // chunk's tiles in turn
     template <class F>
-    __device__ __forceinline__ void score(const Ctx &c, int i, uint32_t s0, uint32_t B, int u0, float shift, F f) const {
+    __device__ __forceinline__ void score(const Ctx &c, const Slot &sl, uint32_t s0, uint32_t B, int u0, float shift, F f) const {
         const int t = threadIdx.x, lane = t & 63, wid = __builtin_amdgcn_readfirstlane(t >> 6);
         const int q = lane >> 4, col = lane & 15, ls = wid * 16 + col;
-        const uint32_t s = s0 + (uint32_t)ls;
-        const int cur = i & 1;
-        const bool live = s < B;
-        const uint32_t at = live ? s : B - 1u;
         uint32_t Bo[KST][4], bd[4];
-        // Img by words; the chunk's own words once more, for the strike-out
-        // (vertices past n2 count as used)
 #pragma unroll
         for (int ks = 0; ks < KST; ++ks) {
-            const int k = 4 * ks + q;
-            const uint32_t im = k < c.w2 ? c.img[cur][(size_t)k * c.Kp + at] : 0u;
-            const uint32_t ph = s_phi[k * GP + ls];
+            const uint32_t ph = s_phi[(4 * ks + q) * GP + ls];
             if (c.code_img == CODE_ONE && c.code_phi == (CODE_ONE | 0x8888u)) {
-                spread_one(im, Bo[ks]);
+                spread_one(sl.im[ks], Bo[ks]);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) Bo[ks][j] |= ((ph >> j) & NIB) << 3;
             } else {
                 uint32_t x[4];
-                spread_slot(im & ~ph, c.code_img, Bo[ks]);
+                spread_slot(sl.im[ks] & ~ph, c.code_img, Bo[ks]);
                 spread_slot(ph, c.code_phi, x);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) Bo[ks][j] |= x[j];
             }
         }
-        const int kd = (u0 >> 5) + q;
-        spread_one((kd < c.w2 ? c.img[cur][(size_t)kd * c.Kp + at] : 0u) | ~below(c.n2, kd), bd);
-        const float base = live ? (float)c.ped[cur][at] + shift : FBIG;
+        spread_one(sl.own, bd);
+        const float base = s0 + (uint32_t)ls < B ? (float)sl.ped + shift : FBIG;
         uint32_t e_lo[4];
         spread_row(1u << col, e_lo);
 #pragma unroll
@@ -216,57 +241,34 @@ __device__ __forceinline__ int level_bins(const Ctx &c, const Level &L, int i, u
 // ------------------------------------------------------------------ expand
 // hist: 0 = only Phi (the complete-then-minimum last level).
 template <int W>
-__global__ __launch_bounds__(WT) void wm_expand(Ctx c, int i, int chunks, int hist) {
-    __shared__ uint32_t s_rows[W * RS], s_phi[W * GP], s_pc[W];
+__global__ __launch_bounds__(WT) void wm_expand(Ctx c, int i, int chunks, int groups, int hist) {
+    __shared__ uint32_t s_rows[W * RS], s_phi[W * GP];
     __shared__ __attribute__((aligned(16))) float s_lc[RS];
     __shared__ uint32_t s_hist[HB];
     __shared__ uint16_t s_nbr[MAXN];
-    __shared__ int s_nw[2];
-    const int t = threadIdx.x, lane = t & 63, wid = __builtin_amdgcn_readfirstlane(t >> 6);
-    const Level L = c.st[i];
-    const uint32_t B = sgpr(L.B), m0 = sgpr(L.m0);
-    const int chunk = blockIdx.x % chunks;
-    const uint32_t s0 = (uint32_t)(blockIdx.x / chunks) * GS;
-    if (s0 >= B) return;
-    const int u0 = chunk * 32 * CWD, cur = i & 1;
-    const int nblk = i / BL, b0 = (int)sgpr(L.b0), c0 = BL * b0;
-    const uint32_t *R1 = c.a1 + (size_t)i * c.w1;
-    const Tile<W> tile{s_rows, s_lc, s_phi};
-    const uint32_t deg = sgpr(degree(c, i));
-    const int nbins = (int)sgpr((uint32_t)level_bins(c, L, i, deg));
-
-    if (t < W) s_pc[t] = 0u;
-    for (int x = t; x < nbins; x += WT) s_hist[x] = 0u;
-    if (hist) tile.stage_rows(c, i, u0);
-    if (wid == NWV - 1) {
-        // the window's neighbours: those of complete blocks, then of the current one
-        int base = 0;
-#pragma unroll 1
-        for (int part = 0; part < 2; ++part) {
-            const int jl = part ? BL * nblk : c0, jh = part ? i : BL * nblk;
-            for (int kw = jl >> 5; kw * 32 < jh; ++kw) {
-                const uint32_t bits = R1[kw] & below(jh, kw) & ~below(jl, kw);
-                const bool mine = lane < 32 && ((bits >> lane) & 1u);
-                const unsigned long long m = __ballot(mine);
-                if (mine) s_nbr[base + (int)__builtin_amdgcn_mbcnt_lo((unsigned)m, 0u)] = (uint16_t)(kw * 32 + lane);
-                base += __popcll(m);
-            }
-            if (lane == 0) s_nw[part] = base;
-        }
-    }
-    __syncthreads();
-    for (int j = t; j < c0; j += WT) {
-        if (!((R1[j >> 5] >> (j & 31)) & 1u)) continue;
-        const uint32_t x = c.com[j];
-        if (x != DEL16) atomicOr(&s_pc[x >> 5], 1u << (x & 31));
-    }
-    __syncthreads();
-    const int slot = t % GS, p0 = t / GS;
+    const int t = threadIdx.x, slot = t % GS, p0 = t / GS;
     constexpr int PT = WT / GS;
-    for (int k = p0; k < W; k += PT) s_phi[k * GP + slot] = s_pc[k];
+    const int chunk = blockIdx.x % chunks, group = blockIdx.x / chunks;
+    const uint32_t s0 = (uint32_t)group * GS;
+    const int u0 = chunk * 32 * CWD, cur = i & 1, nblk = i / BL;
+    const Tile<W> tile{s_rows, s_lc, s_phi};
+    // everything that needs no answer first
+    typename Tile<W>::Slot sl;
+    const Level L = c.st[i];
+    const int nwb = (int)c.prep->nwb, nw = (int)c.prep->nw;
+    const uint32_t deg = sgpr(c.prep->deg);
+    sl.load(c, i, s0, u0);
+    s_nbr[t] = c.prep->nbr[t];
+    for (int k = p0; k < W; k += PT) s_phi[k * GP + slot] = c.prep->pc[k];
+    if (hist) tile.stage_rows(c, i, u0);
+    const uint32_t B = sgpr(L.B), m0 = sgpr(L.m0);
+    if (s0 >= B) return;
+    const int nbins = (int)sgpr((uint32_t)level_bins(c, L, i, deg));
+    for (int x = t; x < nbins; x += WT) s_hist[x] = 0u;
+    for (int x = WT + t; x < nw; x += WT) s_nbr[x] = c.prep->nbr[x];
+    if (chunk == 0 && t < 2) c.cnt[t * groups + group] = 0u;
     __syncthreads();
     {
-        const int nwb = s_nw[0], nw = s_nw[1];
         const uint32_t s = min(s0 + (uint32_t)slot, B - 1u);
         auto put = [&](uint32_t x) {
             if (x != DEL16) atomicOr(&s_phi[(x >> 5) * GP + slot], 1u << (x & 31));
@@ -293,13 +295,14 @@ __global__ __launch_bounds__(WT) void wm_expand(Ctx c, int i, int chunks, int hi
 
     const float shift = (float)((int)(deg * (uint32_t)c.c.edel) - (int)m0), top = (float)(nbins - 1);
     const bool over = nbins == HB;   // children past the last bin are possible
-    tile.score(c, i, s0, B, u0, shift, [&](int, const v4f &y) {
+    tile.score(c, sl, s0, B, u0, shift, [&](int, const v4f &y) {
 #pragma unroll
         for (int r = 0; r < 4; ++r)
             if (y[r] < 8388608.f) atomicAdd(&s_hist[(int)(over ? fminf(y[r], top) : y[r])], 1u);
     });
-    if (chunk == 0 && t < GS && s0 + (uint32_t)t < B) {   // the deletions
-        const uint32_t d = c.ped[cur][s0 + t] - m0 + (uint32_t)c.c.vdel + deg * (uint32_t)c.c.edel;
+    // the deletions: one per slot, from the first k-group's lanes
+    if (chunk == 0 && (t & 63) < 16 && s0 + (uint32_t)((t >> 6) * 16 + (t & 15)) < B) {
+        const uint32_t d = sl.ped - m0 + (uint32_t)c.c.vdel + deg * (uint32_t)c.c.edel;
         atomicAdd(&s_hist[min(d, (uint32_t)(nbins - 1))], 1u);
     }
     __syncthreads();
@@ -322,88 +325,70 @@ __device__ __forceinline__ uint32_t child_ped(const Ctx &c, int i, uint32_t p, i
            (uint32_t)c.c.eins * (in - kept);
 }
 
-// ------------------------------------------------------------------ select
-__global__ __launch_bounds__(ST) void wm_select(Ctx c, int i, int groups) {
-    __shared__ uint32_t s_tmp[ST / 64];
-    __shared__ uint32_t s_bin[HB];
-    __shared__ uint32_t s_res[2], s_first, s_last, s_same;
-    constexpr int PER = HB / ST;
+// ------------------------------------------------------------------ mark
+// The level's threshold from its histogram, by every workgroup; *quota the
+// ties that survive.  Workgroup 0 also writes the next level's size and bounds.
+__device__ __forceinline__ uint32_t threshold(const Ctx &c, int i, const Level &L, uint32_t deg, uint32_t *s_bin) {
+    __shared__ uint32_t s_tmp[NWV], s_res[2], s_first, s_last;
     const int t = threadIdx.x;
-    Level *L = c.st + i, *N = c.st + i + 1;
-    const uint32_t K = c.K, B = L->B, m0 = L->m0;
-    const uint32_t deg = sgpr(degree(c, i));
-    const int nbins = (int)sgpr((uint32_t)level_bins(c, *L, i, deg));
-    const int b0 = (int)L->b0, nblk = i / BL;
+    const uint32_t K = c.K, B = sgpr(L.B), m0 = sgpr(L.m0);
+    const int nbins = (int)sgpr((uint32_t)level_bins(c, L, i, deg));
     if (t == 0) {
         s_first = HB;
         s_last = 0u;
-        s_same = 1u;
+    }
+    // the counts, coalesced, then a thread's own bins from LDS
+    for (int b = t; b < nbins; b += WT) {
+        uint32_t h = 0u;
+#pragma unroll
+        for (int k = 0; k < HC; ++k) h += c.hist[(size_t)k * HB + b];
+        s_bin[b] = h;
     }
     __syncthreads();
-    uint32_t h[PER], sum = 0u, first = HB, last = 0u;
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        const int b = t * PER + q;
-        h[q] = 0u;
-        if (b < nbins) {
-#pragma unroll
-            for (int k = 0; k < HC; ++k) {
-                h[q] += c.hist[(size_t)k * HB + b];
-                c.hist[(size_t)k * HB + b] = 0u;
-            }
-        }
-        sum += h[q];
-        if (h[q]) {
+    const int per = (nbins + WT - 1) / WT;
+    uint32_t sum = 0u, first = HB, last = 0u;
+    for (int q = 0; q < per; ++q) {
+        const int b = t * per + q;
+        const uint32_t h = b < nbins ? s_bin[b] : 0u;
+        sum += h;
+        if (h) {
             first = min(first, (uint32_t)b);
             last = (uint32_t)b;
         }
     }
-    for (int g = t; g < 2 * groups; g += ST) c.cnt[g] = 0u;
-    // the oldest block of the window: one ancestor left?
-    const bool look = b0 < nblk && B <= kCommonMost;
-    if (look) {
-        const uint32_t *a = c.anc[i & 1] + (size_t)b0 * c.Kp;
-        const uint32_t a0 = a[0];
-        bool same = true;
-        for (uint32_t s = t; s < B; s += ST) same = same && a[s] == a0;
-        if (!same) s_same = 0u;
-    }
     uint32_t V;
-    const uint32_t pre = block_excl_scan<ST / 64>(sum, s_tmp, &V);
+    const uint32_t pre = block_excl_scan<NWV>(sum, s_tmp, &V);
     if (sum) {
         atomicMin(&s_first, first);
         atomicMax(&s_last, last);
     }
-    if (V > K && pre < K && K <= pre + sum) {
-        uint32_t under = pre, bin = 0u;
-        bool found = false;
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            if (!found && under + h[q] >= K) {
-                found = true;
-                bin = (uint32_t)q;
+    // the bin of the K-th count, given the counts below this thread's bins
+    auto find = [&](uint32_t under, uint32_t mine, int n) {
+        if (!(under < K && K <= under + mine)) return;
+        for (int q = 0; q < n; ++q) {
+            const int b = t * n + q;
+            const uint32_t h = s_bin[b];   // (the K-th lies in a real bin)
+            if (under + h >= K) {
+                s_res[0] = (uint32_t)b;
+                s_res[1] = under;
+                break;
             }
-            if (!found) under += h[q];
+            under += h;
         }
-        s_res[0] = (uint32_t)(t * PER) + bin;
-        s_res[1] = under;
-    }
-    __syncthreads();
-    const bool common = look && s_same != 0u;
-    if (common && t < BL) {
-        const int j = BL * b0 + t;
-        c.com[j] = c.phi[(size_t)j * c.Kp + c.anc[i & 1][(size_t)b0 * c.Kp]];
-    }
+    };
     const bool all = V <= K;
+    if (!all) find(pre, sum, per);
+    __syncthreads();
     uint32_t T = all ? NONE : m0 + s_res[0], under = all ? 0u : s_res[1];
     if (nbins == HB && !all && s_res[0] == (uint32_t)(HB - 1)) {
         // the K-th child is past the range: count the children 4096 values at
         // a time (from the last bin's first value on) until it is found
+        constexpr int PER = HB / WT;
         for (uint32_t lo = m0 + HB - 1;; lo += HB) {
             __syncthreads();
-            for (int b = t; b < HB; b += ST) s_bin[b] = 0u;
+            for (int b = t; b < HB; b += WT) s_bin[b] = 0u;
             __syncthreads();
-            for (uint32_t x = t; x < B * (uint32_t)(c.n2 + 1); x += ST) {
+            for (uint32_t x = t; x < B * (uint32_t)(c.n2 + 1); x += WT) {
                 const uint32_t p = x % B;
                 const int u = (int)(x / B);
                 uint32_t d;
@@ -417,78 +402,66 @@ __global__ __launch_bounds__(ST) void wm_select(Ctx c, int i, int groups) {
             }
             __syncthreads();
             uint32_t mine = 0u, tot;
-#pragma unroll
             for (int q = 0; q < PER; ++q) mine += s_bin[t * PER + q];
-            const uint32_t below_me = under + block_excl_scan<ST / 64>(mine, s_tmp, &tot);
+            const uint32_t below_me = under + block_excl_scan<NWV>(mine, s_tmp, &tot);
             if (under + tot < K) {
                 under += tot;
                 continue;
             }
-            if (below_me < K && K <= below_me + mine) {
-                uint32_t a = below_me;
-                for (int q = 0; q < PER; ++q) {
-                    const uint32_t x = s_bin[t * PER + q];
-                    if (a + x >= K) {
-                        s_res[0] = (uint32_t)(t * PER + q);
-                        s_res[1] = a;
-                        break;
-                    }
-                    a += x;
-                }
-            }
+            find(below_me, mine, PER);
             __syncthreads();
             T = lo + s_res[0];
             under = s_res[1];
             break;
         }
     }
-    if (t == 0) {
-        L->V = V;
-        L->T = T;
-        L->quota = all ? 0u : K - under;
+    if (blockIdx.x == 0 && t == 0) {
+        Level *N = c.st + i + 1;
+        c.st[i].quota = all ? 0u : K - under;
         N->B = min(V, K);
         N->m0 = m0 + s_first;
         // (the last bin also holds what is above it)
         N->mmax = all ? (s_last == (uint32_t)(HB - 1) ? c.pedmax : m0 + s_last) : T;
-        N->b0 = (uint32_t)b0 + (common ? 1u : 0u);
         *c.ce += V;
     }
+    return T;
 }
 
-// ------------------------------------------------------------------ mark
 template <int W>
 __global__ __launch_bounds__(WT) void wm_mark(Ctx c, int i, int chunks, int groups) {
     __shared__ uint32_t s_rows[W * RS], s_phi[W * GP];
     __shared__ __attribute__((aligned(16))) float s_lc[RS];
+    __shared__ uint32_t s_bin[HB];
     __shared__ uint32_t s_le[CWD * GP], s_lt[CWD * GP];
     __shared__ uint32_t s_cnt[2];
     const int t = threadIdx.x, lane = t & 63, wid = __builtin_amdgcn_readfirstlane(t >> 6);
-    const Level L = c.st[i];
-    const uint32_t B = sgpr(L.B), T = sgpr(L.T);
     const int chunk = blockIdx.x % chunks, group = blockIdx.x / chunks;
     const uint32_t s0 = (uint32_t)group * GS;
-    if (s0 >= B) return;
     const int u0 = chunk * 32 * CWD, cur = i & 1;
-    const uint32_t deg = sgpr(degree(c, i));
-    const Tile<W> tile{s_rows, s_lc, s_phi};
     const int slot = t % GS, p0 = t / GS;
     constexpr int PT = WT / GS;
-    const uint32_t s = s0 + (uint32_t)slot, at = min(s, B - 1u);
-    if (T != NONE) {
-        tile.stage_rows(c, i, u0);
-        for (int k = p0; k < W; k += PT) s_phi[k * GP + slot] = k < c.w2 ? c.sets[(size_t)k * c.Kp + at] : 0u;
-    }
+    const uint32_t s = s0 + (uint32_t)slot;
+    const Tile<W> tile{s_rows, s_lc, s_phi};
+    typename Tile<W>::Slot sl;
+    const Level L = c.st[i];
+    const uint32_t deg = sgpr(c.prep->deg);
+    sl.load(c, i, s0, u0);
+    const uint32_t ped = c.ped[cur][s];
+    tile.stage_rows(c, i, u0);
+    for (int k = p0; k < W; k += PT) s_phi[k * GP + slot] = k < c.w2 ? c.sets[(size_t)k * c.Kp + s] : 0u;
     for (int x = t; x < CWD * GP; x += WT) {
         s_le[x] = 0u;
         s_lt[x] = 0u;
     }
     if (t < 2) s_cnt[t] = 0u;
-    __syncthreads();
+    const uint32_t B = sgpr(L.B);
+    if (s0 >= B) return;
+    const uint32_t T = sgpr(threshold(c, i, L, deg, s_bin));   // (waits for the staging too)
     if (T != NONE) {
         // bytes: 0 below T, 1 at T, more above
         const float shift = (float)((int)(deg * (uint32_t)c.c.edel) - (int)T + 1);
         const int ls = wid * 16 + (lane & 15), q = lane >> 4;
-        tile.score(c, i, s0, B, u0, shift, [&](int k, const v4f &y) {
+        tile.score(c, sl, s0, B, u0, shift, [&](int k, const v4f &y) {
             uint32_t w = 0u;
 #pragma unroll
             for (int r = 0; r < 4; ++r) w = __builtin_amdgcn_cvt_pk_u8_f32(fminf(y[r], (float)XCAP), r, w);
@@ -516,7 +489,7 @@ __global__ __launch_bounds__(WT) void wm_mark(Ctx c, int i, int chunks, int grou
         ne += (uint32_t)__popc(a & ~b);
     }
     if (chunk == 0 && p0 == 0 && s < B) {
-        const uint32_t d = c.ped[cur][s] + (uint32_t)c.c.vdel + deg * (uint32_t)c.c.edel;
+        const uint32_t d = ped + (uint32_t)c.c.vdel + deg * (uint32_t)c.c.edel;
         const uint32_t a = d <= T ? 1u : 0u, b = d < T ? 1u : 0u;
         c.le[(size_t)c.w2 * c.Kp + s] = a;
         c.lt[(size_t)c.w2 * c.Kp + s] = b;
@@ -572,39 +545,128 @@ __device__ __forceinline__ void write_slot(const Ctx &c, int i, uint32_t s, uint
 }
 
 // ------------------------------------------------------------------ update
-template <int W>
-__global__ __launch_bounds__(WT) void wm_update(Ctx c, int i, int groups) {
-    __shared__ uint32_t s_tmp[NWV];
-    constexpr int PT = WT / GS;
-    constexpr int CWM = (W + 1 + PT - 1) / PT;   // mask words of a thread
-    const int t = threadIdx.x, us = t / PT, part = t % PT;
-    const Level L = c.st[i];
-    const uint32_t B = sgpr(L.B), quota = sgpr(L.quota), Bn = sgpr(c.st[i + 1].B);
-    const int b0 = (int)sgpr(c.st[i + 1].b0);
-    const uint32_t s0 = (uint32_t)blockIdx.x * GS;
-    if (s0 >= B) return;
-    const uint32_t deg = sgpr(degree(c, i));
-    // counts of the groups before this one
-    uint32_t a = 0u, e = 0u, LT, EQ;
-    for (int g = t; g < (int)blockIdx.x; g += WT) {
-        a += c.cnt[g];
-        e += c.cnt[groups + g];
+// The next level's Prep, by one workgroup: whether the oldest block has one
+// ancestor left in the whole beam, the common images of v = i + 1's earlier
+// neighbours, and the window's neighbours.
+template <int UT>
+__device__ __forceinline__ void prepare(const Ctx &c, int i) {
+    __shared__ uint32_t s_pc[MAXN / 32], s_same;
+    const int t = threadIdx.x, lane = t & 63, wid = t >> 6, v = i + 1;
+    int b0 = (int)c.st[i].b0;
+    const uint32_t B = c.st[i].B;
+    const uint32_t *R = c.a1 + (size_t)min(v, c.n1 - 1) * c.w1;
+    const bool look = b0 < i / BL && B <= kCommonMost;
+    if (t == 0) s_same = 1u;
+    if (t < MAXN / 32) s_pc[t] = 0u;
+    __syncthreads();
+    if (look) {
+        const uint32_t *a = c.anc[i & 1] + (size_t)b0 * c.Kp;
+        const uint32_t a0 = a[0];
+        uint32_t differ = 0u;
+#pragma unroll 4
+        for (uint32_t s = t; s < B; s += UT) differ |= a[s] ^ a0;
+        if (differ) s_same = 0u;
     }
-    (void)block_excl_scan<NWV>(a, s_tmp, &LT);
-    (void)block_excl_scan<NWV>(e, s_tmp, &EQ);
-    const uint32_t s = s0 + (uint32_t)us;
+    __syncthreads();
+    if (look && s_same != 0u) {
+        const int j = BL * b0 + t;
+        if (t < BL) c.com[j] = c.phi[(size_t)j * c.Kp + c.anc[i & 1][(size_t)b0 * c.Kp]];
+        ++b0;
+    }
+    if (t == 0) c.st[v].b0 = (uint32_t)b0;
+    __syncthreads();
+    if (v >= c.n1) return;
+    const int c0 = BL * b0, nblk = v / BL;
+    for (int j = t; j < c0; j += UT) {
+        if (!((R[j >> 5] >> (j & 31)) & 1u)) continue;
+        const uint32_t x = c.com[j];
+        if (x != DEL16) atomicOr(&s_pc[x >> 5], 1u << (x & 31));
+    }
+    if (wid == UT / 64 - 1) {
+        int base = 0;
+#pragma unroll 1
+        for (int part = 0; part < 2; ++part) {
+            const int jl = part ? BL * nblk : c0, jh = part ? v : BL * nblk;
+            for (int kw = jl >> 5; kw * 32 < jh; ++kw) {
+                const uint32_t bits = R[kw] & below(jh, kw) & ~below(jl, kw);
+                const bool mine = lane < 32 && ((bits >> lane) & 1u);
+                const unsigned long long m = __ballot(mine);
+                if (mine) c.prep->nbr[base + (int)__builtin_amdgcn_mbcnt_lo((unsigned)m, 0u)] = (uint16_t)(kw * 32 + lane);
+                base += __popcll(m);
+            }
+            if (lane == 0) (part ? c.prep->nw : c.prep->nwb) = (uint32_t)base;
+        }
+        const uint32_t deg = degree(c, v);
+        if (lane == 0) c.prep->deg = deg;
+    }
+    __syncthreads();
+    if (t < MAXN / 32) c.prep->pc[t] = s_pc[t];
+}
+
+// The last workgroup prepares the next level; deg comes with the launch's own
+// reading of it, since Prep is being rewritten.
+// UT threads: 1024 while there are few groups, since the survivors gather
+// under few parents and a workgroup writes UT / 4 slots at a time.
+template <int W, int UT>
+__global__ __launch_bounds__(UT) void wm_update(Ctx c, int i, int groups) {
+    __shared__ uint32_t s_tmp[4][UT / 64];
+    constexpr int NWU = UT / 64, PT = UT / GS;
+    constexpr int CWM = (W + 1 + PT - 1) / PT;   // mask words of a thread
+    const int t = threadIdx.x, us = t / PT, part = t % PT, wid = t >> 6, lane = t & 63;
+    if (blockIdx.x == gridDim.x - 1) {
+        prepare<UT>(c, i);
+        return;
+    }
+    const uint32_t s0 = (uint32_t)blockIdx.x * GS, s = s0 + (uint32_t)us;
+    const Level L = c.st[i];
+    const uint32_t Bn0 = c.st[i + 1].B;
     uint32_t ml[CWM], me[CWM], nl = 0u, ne = 0u;
 #pragma unroll
     for (int k = 0; k < CWM; ++k) {
         const int kw = part * CWM + k;
-        const bool in = s < B && kw <= c.w2;
-        ml[k] = in ? c.lt[(size_t)kw * c.Kp + s] : 0u;
-        me[k] = in ? c.le[(size_t)kw * c.Kp + s] & ~ml[k] : 0u;
+        ml[k] = kw <= c.w2 ? c.lt[(size_t)kw * c.Kp + s] : 0u;
+        me[k] = kw <= c.w2 ? c.le[(size_t)kw * c.Kp + s] : 0u;
+    }
+    // counts of the groups before this one
+    uint32_t a = 0u, e = 0u;
+    for (int g = t; g < (int)blockIdx.x; g += UT) {
+        a += c.cnt[g];
+        e += c.cnt[groups + g];
+    }
+    for (uint32_t b = blockIdx.x * UT + t; b < (uint32_t)(HC * HB); b += (gridDim.x - 1) * UT) c.hist[b] = 0u;
+    const uint32_t deg = sgpr(degree(c, i));
+    const uint32_t B = sgpr(L.B), quota = sgpr(L.quota), Bn = sgpr(Bn0);
+    const int b0 = (int)sgpr(L.b0);
+    if (s0 >= B) return;
+#pragma unroll
+    for (int k = 0; k < CWM; ++k) {
+        ml[k] = s < B ? ml[k] : 0u;
+        me[k] = s < B ? me[k] & ~ml[k] : 0u;
         nl += (uint32_t)__popc(ml[k]);
         ne += (uint32_t)__popc(me[k]);
     }
-    uint32_t tl, te;
-    const uint32_t pl = block_excl_scan<NWV>(nl, s_tmp, &tl), pe = block_excl_scan<NWV>(ne, s_tmp, &te);
+    // one pass for the sums before the group and the scans inside it
+    uint32_t pl = (uint32_t)wave_excl_scan((int)nl), pe = (uint32_t)wave_excl_scan((int)ne);
+    a = wave_sum(a);
+    e = wave_sum(e);
+    if (lane == 63) {
+        s_tmp[0][wid] = pl + nl;
+        s_tmp[1][wid] = pe + ne;
+        s_tmp[2][wid] = a;
+        s_tmp[3][wid] = e;
+    }
+    __syncthreads();
+    uint32_t LT = 0u, EQ = 0u, tl = 0u, te = 0u;
+#pragma unroll
+    for (int k = 0; k < NWU; ++k) {
+        const uint32_t x = s_tmp[0][k], y = s_tmp[1][k];
+        pl += k < wid ? x : 0u;
+        pe += k < wid ? y : 0u;
+        tl += x;
+        te += y;
+        LT += s_tmp[2][k];
+        EQ += s_tmp[3][k];
+    }
     const uint32_t out0 = LT + min(EQ, quota), out1 = LT + tl + min(EQ + te, quota);
     const uint32_t eqb = min(EQ + pe, quota);   // ties kept before this thread's words
     uint32_t keq = min(quota - eqb, ne);        // ... and among them
@@ -626,9 +688,9 @@ __global__ __launch_bounds__(WT) void wm_update(Ctx c, int i, int groups) {
         }
     }
     __syncthreads();
-    for (uint32_t x = out0 + (uint32_t)us; x < min(out1, Bn); x += GS) {
+    for (uint32_t x = out0 + (uint32_t)(t / 4); x < min(out1, Bn); x += UT / 4) {
         const uint32_t r = c.rec[x];
-        write_slot(c, i, x, r >> UBITS, (int)(r & ((1u << UBITS) - 1u)), deg, b0, part);
+        write_slot(c, i, x, r >> UBITS, (int)(r & ((1u << UBITS) - 1u)), deg, b0, t & 3);
     }
 }
 
@@ -762,7 +824,7 @@ __global__ __launch_bounds__(WT) void wm_final_map(Ctx c, int groups) {
 // ------------------------------------------------------------------ host side
 
 struct Layout {
-    size_t ped[2], nsub[2], img[2], cur[2], anc[2], phi, com, sets, le, lt, cnt, rec, hist, st, ce, best, total;
+    size_t ped[2], nsub[2], img[2], cur[2], anc[2], phi, com, sets, le, lt, cnt, rec, hist, st, prep, ce, best, total;
 };
 
 uint32_t slot_stride(int K) { return (uint32_t)((K + GS - 1) / GS) * GS; }
@@ -792,6 +854,7 @@ Layout layout(int n1, int w2, uint32_t Kp) {
     L.rec = take((size_t)Kp * 4);
     L.hist = take((size_t)HC * HB * 4);
     L.st = take((size_t)(n1 + 1) * sizeof(Level));
+    L.prep = take(sizeof(Prep));
     L.ce = take(8);
     L.best = take(groups * 8);
     L.total = off;
@@ -806,16 +869,18 @@ hipError_t levels(const Ctx &c, bool last_complete, hipStream_t stream) {
     for (int i = 0; i < c.n1; ++i) {
         const int g = (int)((bound + GS - 1) / GS);
         const bool last = last_complete && i == c.n1 - 1;
-        hipLaunchKernelGGL(wm_expand<W>, dim3(last ? g : g * chunks), dim3(WT), 0, stream, c, i, last ? 1 : chunks, last ? 0 : 1);
+        hipLaunchKernelGGL(wm_expand<W>, dim3(last ? g : g * chunks), dim3(WT), 0, stream, c, i, last ? 1 : chunks, groups, last ? 0 : 1);
         if (last) {
             hipLaunchKernelGGL(wm_complete, dim3(g), dim3(WT), 0, stream, c, i);
             hipLaunchKernelGGL(wm_pick, dim3(1), dim3(WT), 0, stream, c, i, g);
             bound = 1;
             break;
         }
-        hipLaunchKernelGGL(wm_select, dim3(1), dim3(ST), 0, stream, c, i, groups);
         hipLaunchKernelGGL(wm_mark<W>, dim3(g * chunks), dim3(WT), 0, stream, c, i, chunks, groups);
-        hipLaunchKernelGGL(wm_update<W>, dim3(g), dim3(WT), 0, stream, c, i, groups);
+        if (g <= 512)
+            hipLaunchKernelGGL((wm_update<W, 1024>), dim3(g + 1), dim3(1024), 0, stream, c, i, groups);
+        else
+            hipLaunchKernelGGL((wm_update<W, 256>), dim3(g + 1), dim3(256), 0, stream, c, i, groups);
         const uint64_t grown = bound * (uint64_t)(c.n2 + 1);
         bound = grown < c.K ? grown : c.K;
     }
@@ -882,6 +947,7 @@ hipError_t launch_widem(const DbView &src, const DbView &dst, const GraphRec &g1
     c.rec = reinterpret_cast<uint32_t *>(base + L.rec);
     c.hist = reinterpret_cast<uint32_t *>(base + L.hist);
     c.st = reinterpret_cast<Level *>(base + L.st);
+    c.prep = reinterpret_cast<Prep *>(base + L.prep);
     c.ce = reinterpret_cast<unsigned long long *>(base + L.ce);
     c.best = reinterpret_cast<unsigned long long *>(base + L.best);
     c.out_dist = dist;
