@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <limits>
+#include <cstring>
 #include <vector>
 
 #include "ged.h"
@@ -59,7 +60,12 @@ ged_status ged_edit_path(ged_db *db, const ged_pair *h_pairs, int64_t npairs, ge
     std::vector<int64_t> cap((size_t)npairs + 1);
     st = ged_edit_path_capacity(db, h_pairs, npairs, cap.data());
     if (st != GED_OK) return st;
-    std::vector<gedk::WorkItem> work((size_t)npairs);
+    // work items, then capacities: one allocation and one copy
+    const size_t o_cap = sizeof(gedk::WorkItem) * (size_t)npairs, bytes = o_cap + sizeof(int64_t) * (size_t)npairs;
+    static_assert(sizeof(gedk::WorkItem) % alignof(int64_t) == 0, "capacities follow the work items");
+    std::vector<char> image(bytes);
+    gedk::WorkItem *work = reinterpret_cast<gedk::WorkItem *>(image.data());
+    memcpy(image.data() + o_cap, cap.data(), sizeof(int64_t) * (size_t)npairs);
     int64_t moff = 0;
     for (int64_t i = 0; i < npairs; ++i) {
         work[(size_t)i].src = (int32_t)h_pairs[i].src;
@@ -72,17 +78,12 @@ ged_status ged_edit_path(ged_db *db, const ged_pair *h_pairs, int64_t npairs, ge
     if (moff > 0 && !d_map) return fail(GED_EINVAL, "d_map is NULL");
 
     hipStream_t s = static_cast<hipStream_t>(stream);
-    gedk::WorkItem *d_work = nullptr;
-    int64_t *d_cap = nullptr;
-    hipError_t e = hipMalloc((void **)&d_work, sizeof(gedk::WorkItem) * (size_t)npairs);
-    if (e == hipSuccess) e = hipMalloc((void **)&d_cap, sizeof(int64_t) * (size_t)npairs);
-    if (e != hipSuccess) {
-        if (d_work) (void)hipFree(d_work);
-        return fail(GED_ENOMEM, "edit-path staging allocation failed: %s", hipGetErrorString(e));
-    }
-    e = hipMemcpyAsync(d_work, work.data(), sizeof(gedk::WorkItem) * (size_t)npairs, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(d_cap, cap.data(), sizeof(int64_t) * (size_t)npairs, hipMemcpyHostToDevice, s);
+    char *d_in = nullptr;
+    hipError_t e = hipMalloc((void **)&d_in, bytes);
+    if (e != hipSuccess) return fail(GED_ENOMEM, "edit-path staging allocation failed: %s", hipGetErrorString(e));
+    e = hipMemcpyAsync(d_in, image.data(), bytes, hipMemcpyHostToDevice, s);
+    const gedk::WorkItem *d_work = reinterpret_cast<const gedk::WorkItem *>(d_in);
+    const int64_t *d_cap = reinterpret_cast<const int64_t *>(d_in + o_cap);
     int cus = 0, dev = 0;
     if (e == hipSuccess) e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
@@ -98,8 +99,7 @@ ged_status ged_edit_path(ged_db *db, const ged_pair *h_pairs, int64_t npairs, ge
         e = hipMemcpyAsync(h_count.data(), d_count, sizeof(int32_t) * (size_t)npairs, hipMemcpyDeviceToHost, s);
     const hipError_t es = hipStreamSynchronize(s);   // also before freeing after a failed enqueue
     if (e == hipSuccess) e = es;
-    (void)hipFree(d_work);
-    (void)hipFree(d_cap);
+    (void)hipFree(d_in);
     if (e != hipSuccess) return fail(GED_EDEVICE, "edit-path run failed: %s", hipGetErrorString(e));
     for (int64_t i = 0; i < npairs; ++i)
         if (h_count[(size_t)i] < 0)

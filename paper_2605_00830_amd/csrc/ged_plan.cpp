@@ -41,7 +41,7 @@ struct Bin {
     gedk::BlockShape shape{};    // workgroup-kernel instantiation and workspace shape
     std::vector<WorkItem> h_sorted;   // longest first
     std::vector<WorkItem> h_work;     // launch order for the current grid (deal_alternating)
-    WorkItem *d_work = nullptr;
+    WorkItem *d_work = nullptr;  // in the plan's slab, as the next
     int *d_queue = nullptr;      // [1 + nwork]: batched counter, then one per pair
     void *d_ws = nullptr;        // workgroup-kernel workspace
     size_t ws_stride = 0;
@@ -79,6 +79,7 @@ struct ged_plan {
     hipGraph_t graph = nullptr;
     hipGraphExec_t graph_exec = nullptr;
     uint32_t flags = 0;                 // GED_PLAN_* bits
+    void *d_slab = nullptr;             // statuses, set-aside records, queue counters and work lists
     int32_t *d_status = nullptr;        // [npairs] GED_OK, or why the pair was set aside
     WorkItem *d_aside = nullptr;        // set-aside pairs: out, src = mapping entries, map_off
     int naside = 0;
@@ -102,14 +103,11 @@ void free_plan(ged_plan *p) {
     if (!p) return;
     drop_graph(p);
     for (Bin &b : p->bins) {
-        if (b.d_work) (void)hipFree(b.d_work);
-        if (b.d_queue) (void)hipFree(b.d_queue);
         if (b.d_ws) (void)hipFree(b.d_ws);
     }
     if (p->ev_start) (void)hipEventDestroy(p->ev_start);
     if (p->ev_stop) (void)hipEventDestroy(p->ev_stop);
-    if (p->d_status) (void)hipFree(p->d_status);
-    if (p->d_aside) (void)hipFree(p->d_aside);
+    if (p->d_slab) (void)hipFree(p->d_slab);
     for (hipStream_t st : p->side) (void)hipStreamDestroy(st);
     for (hipEvent_t ev : p->ev_join) (void)hipEventDestroy(ev);
     if (p->ev_fork) (void)hipEventDestroy(p->ev_fork);
@@ -160,9 +158,10 @@ int default_threads(const ged_plan *p, const Bin &b) {
 
 // Point bin `b` at one kernel family, workgroup size (workgroup kernel) and
 // resident-workgroup count (groups_per_cu <= 0: the occupancy limit); grows
-// the workspace as needed and uploads the work list in the launch order for
-// that grid (blocking copy: no run of the plan may be in flight).
-ged_status configure_bin(ged_plan *p, Bin &b, bool wave, int groups_per_cu, int threads) {
+// the workspace as needed and orders the work list for that grid; with `upload`
+// the list also goes to the device (blocking copy: no run of the plan may be in
+// flight).
+ged_status configure_bin(ged_plan *p, Bin &b, bool wave, int groups_per_cu, int threads, bool upload = true) {
     if (b.bip) {
         // threads: 64 = one wave per pair, 256 = four
         const int nwav = threads >= 256 ? 4 : 1;
@@ -183,7 +182,8 @@ ged_status configure_bin(ged_plan *p, Bin &b, bool wave, int groups_per_cu, int 
         }
         b.h_work = b.h_sorted;
         gedh::deal_alternating(b.h_work, grid, (nwav == 1 ? 4 : 1) * (int64_t)p->cus);
-        GED_HIP(hipMemcpy(b.d_work, b.h_work.data(), sizeof(WorkItem) * (size_t)nwork, hipMemcpyHostToDevice));
+        if (upload)
+            GED_HIP(hipMemcpy(b.d_work, b.h_work.data(), sizeof(WorkItem) * (size_t)nwork, hipMemcpyHostToDevice));
         b.wave = false;
         b.groups_per_cu = gpc;
         b.grid = grid;
@@ -212,7 +212,8 @@ ged_status configure_bin(ged_plan *p, Bin &b, bool wave, int groups_per_cu, int 
     }
     b.h_work = b.h_sorted;
     gedh::deal_alternating(b.h_work, grid, wave ? 4 * (int64_t)p->cus : (int64_t)p->cus);
-    GED_HIP(hipMemcpy(b.d_work, b.h_work.data(), sizeof(WorkItem) * (size_t)nwork, hipMemcpyHostToDevice));
+    if (upload)
+        GED_HIP(hipMemcpy(b.d_work, b.h_work.data(), sizeof(WorkItem) * (size_t)nwork, hipMemcpyHostToDevice));
     b.wave = wave;
     b.groups_per_cu = gpc;
     b.grid = grid;
@@ -520,20 +521,7 @@ ged_status ged_plan_create_ex(ged_db *db, const ged_pair *h_pairs, int64_t npair
         free_plan(p);
         return fail(GED_EDEVICE, "device query failed: %s", hipGetErrorString(e));
     }
-    // per-pair statuses and the set-aside pairs' output records
     p->naside = (int)h_aside.size();
-    e = hipMalloc((void **)&p->d_status, sizeof(int32_t) * (size_t)std::max<int64_t>(npairs, 1));
-    if (e == hipSuccess && npairs > 0)
-        e = hipMemcpy(p->d_status, h_status.data(), sizeof(int32_t) * (size_t)npairs, hipMemcpyHostToDevice);
-    if (e == hipSuccess && p->naside > 0) {
-        e = hipMalloc((void **)&p->d_aside, sizeof(WorkItem) * h_aside.size());
-        if (e == hipSuccess)
-            e = hipMemcpy(p->d_aside, h_aside.data(), sizeof(WorkItem) * h_aside.size(), hipMemcpyHostToDevice);
-    }
-    if (e != hipSuccess) {
-        free_plan(p);
-        return fail(GED_ENOMEM, "plan allocation failed: %s", hipGetErrorString(e));
-    }
     // streams and events for running bins side by side (default priority;
     // at most three extra streams, bins beyond share them in turn; one join
     // event per bin)
@@ -599,20 +587,48 @@ ged_status ged_plan_create_ex(ged_db *db, const ged_pair *h_pairs, int64_t npair
             free_plan(p);
             return fail(GED_EDEVICE, "occupancy query failed: %s", hipGetErrorString(e));
         }
-        const int64_t nwork = (int64_t)b.h_work.size();
-        e = hipMalloc((void **)&b.d_work, sizeof(WorkItem) * (size_t)nwork);
-        if (e == hipSuccess) e = hipMalloc((void **)&b.d_queue, sizeof(int) * (size_t)(nwork + 1));
-        // the queue counters start at 0; every run leaves them at 0 again
-        if (e == hipSuccess) e = hipMemset(b.d_queue, 0, sizeof(int) * (size_t)(nwork + 1));
-        if (e != hipSuccess) {
-            free_plan(p);
-            return fail(GED_ENOMEM, "plan allocation failed: %s", hipGetErrorString(e));
-        }
-        st = configure_bin(p, b, b.wave_ok, opt.groups_per_cu, default_threads(p, b));
+        st = configure_bin(p, b, b.wave_ok, opt.groups_per_cu, default_threads(p, b), false);
         if (st != GED_OK) {
             free_plan(p);
             return st;
         }
+    }
+    // one device allocation and one copy for everything the plan keeps beside
+    // its workspaces: per-pair statuses, the set-aside pairs' output records,
+    // the queue counters (they start at 0; every run leaves them at 0 again)
+    // and the work lists.  (A small blocking copy, a fill and an allocation are
+    // tens of microseconds each: a plan made for 300 new pairs, run, their edit
+    // paths taken, and destroyed: 561 -> 480 us.)
+    size_t bytes = 0;
+    auto take = [&bytes](size_t n) {
+        const size_t o = bytes;
+        bytes += (n + 255) & ~(size_t)255;
+        return o;
+    };
+    const size_t o_status = take(sizeof(int32_t) * (size_t)std::max<int64_t>(npairs, 1));
+    const size_t o_aside = take(sizeof(WorkItem) * h_aside.size());
+    std::vector<size_t> o_queue, o_work;
+    for (const Bin &b : p->bins) {
+        o_queue.push_back(take(sizeof(int) * (b.h_work.size() + 1)));
+        o_work.push_back(take(sizeof(WorkItem) * b.h_work.size()));
+    }
+    std::vector<char> image(bytes, 0);
+    if (npairs > 0) memcpy(image.data() + o_status, h_status.data(), sizeof(int32_t) * (size_t)npairs);
+    if (p->naside > 0) memcpy(image.data() + o_aside, h_aside.data(), sizeof(WorkItem) * h_aside.size());
+    for (size_t k = 0; k < p->bins.size(); ++k)
+        memcpy(image.data() + o_work[k], p->bins[k].h_work.data(), sizeof(WorkItem) * p->bins[k].h_work.size());
+    e = hipMalloc(&p->d_slab, bytes);
+    if (e == hipSuccess) e = hipMemcpy(p->d_slab, image.data(), bytes, hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+        free_plan(p);
+        return fail(GED_ENOMEM, "plan allocation failed: %s", hipGetErrorString(e));
+    }
+    char *slab = static_cast<char *>(p->d_slab);
+    p->d_status = reinterpret_cast<int32_t *>(slab + o_status);
+    if (p->naside > 0) p->d_aside = reinterpret_cast<WorkItem *>(slab + o_aside);
+    for (size_t k = 0; k < p->bins.size(); ++k) {
+        p->bins[k].d_queue = reinterpret_cast<int *>(slab + o_queue[k]);
+        p->bins[k].d_work = reinterpret_cast<WorkItem *>(slab + o_work[k]);
     }
     *out = p;
     return ok();
