@@ -44,16 +44,27 @@
 // per level instead of once per slot.  (Measured window: 35 to 85 levels on
 // 200- to 450-vertex pairs at K = 256, against half of n1 for a full copy.)
 //
+// Images that became common are used in every slot, so their vertices need no
+// scoring: target vertices stand in the rows, labels and used bits by position,
+// and every CB = 4 blocks the common ones move behind the others (in place,
+// order kept, so generation order is still ascending position).  The tiles past
+// the nact positions left are skipped.  Fewer blocks at a time would seldom free
+// a group of tiles (32 or 64 vertices).  (Mean nact at 500 vertices and K = 256:
+// 369; at 250 and K = 64: 177.  With the clamp as one med3 instead of min and
+// the max that quiets NaN: 256 pairs of 100..500 vertices, K = 256 14,181 ->
+// 12,555 us; 512 of 65..250, K = 64 2,165 -> 2,060; 3000 of 10..70, which have
+// no level for it, 746 -> 740.)
+//
 // Measured against the candidate-matrix kernel of kb_block.hip (same box, us
-// a launch): 256 pairs of 100..500 vertices at K = 256 82,396 -> 13,909; 512
-// pairs of 65..250 at K = 64 9,293 -> 2,168; 400 pairs of 65..128 at K = 1024
-// 20,034 -> 6,379; 100 labelled pairs of 300..500 at K = 64 131,104 -> 12,191;
-// 200 labelled directed pairs of 130..250 at K = 80 41,755 -> 5,939.  A launch
-// lasts as long as its largest pair.  A level at 500 vertices, K = 256 is about
-// 58 thousand cycles: 29.7 in the scoring (the matrix instructions, 16 cycles
-// each, and the vector ones do not overlap on this part: the two add up), 5.7
-// in 1.36 threshold rounds, 4.5 marking survivors, 3.5 emitting, 6.4 in the
-// update, 7.7 building Phi.
+// a launch): 256 pairs of 100..500 vertices at K = 256 81,900 -> 12,560; 512
+// pairs of 65..250 at K = 64 9,290 -> 2,060; and before the positions closed up
+// 400 pairs of 65..128 at K = 1024 20,034 -> 6,379; 100 labelled pairs of
+// 300..500 at K = 64 131,104 -> 12,191; 200 labelled directed pairs of 130..250
+// at K = 80 41,755 -> 5,939.  A launch lasts as long as its largest pair.  A
+// level at 500 vertices, K = 256 is about 54 thousand cycles: 24.9 in the
+// scoring (the matrix instructions, 16 cycles each, and the vector ones do not
+// overlap on this part: the two add up), 5.5 in 1.4 threshold rounds, 4.8
+// marking survivors, 3.5 emitting, 7.1 in the update, 5.8 building Phi.
 #pragma once
 
 #include "ged_internal.h"
@@ -74,6 +85,7 @@ constexpr uint32_t DEL16 = 0xffffu;
 constexpr int XCAP = 127;                   // byte of a child above the range
 constexpr int DELU = 1023;                  // survivor record's vertex of the deletion child
 constexpr int BL = 8;                       // levels per mapping block
+constexpr int CB = 4;                       // mapping blocks whose images leave the positions together
 constexpr int SC_ONE = 127;                 // E8M0 scales 1, 2^24
 constexpr int SC_BIG = 127 + 24;
 constexpr uint32_t CODE_ONE = 0x4124u;      // slot operand's nibbles of weight 1 (spread_slot)
@@ -87,7 +99,7 @@ constexpr int slot_pad(int KS) { return KS % 64 == 0 ? KS + 16 : (KS == 32 ? 48 
 // KS slots, NA sets, ND rows of a vertex); the ancestor rows, whose number goes
 // with the largest source, come last.
 struct MatLds {
-    int rows, lc, l1, l2, r1, img, phi, le, lt, cur, com, nbr, nbc, pc, ped, nsub, sel, anc;
+    int rows, lc, l1, l2, r1, act, img, use, phi, le, lt, cur, com, nbr, nbc, pc, ped, nsub, sel, anc;
 };
 constexpr MatLds mat_lds(int W, int KS, int NA, int ND) {
     MatLds L{};
@@ -103,7 +115,9 @@ constexpr MatLds mat_lds(int W, int KS, int NA, int ND) {
     L.l1 = take(N1 * 4);
     L.l2 = take(URS * 4);
     L.r1 = take(2 * ND * NA * (N1 / 32) * 4);
+    L.act = take(URS * 2);
     L.img = take(W * KP * 4);
+    L.use = take(WU * KP * 4);
     L.phi = take(NA * W * KP * 4);
     L.le = take((WU + 1) * KP * 4);
     L.lt = take((WU + 1) * KP * 4);
@@ -185,6 +199,10 @@ __device__ __forceinline__ unsigned long long wave_min64(unsigned long long v) {
     return v;
 }
 
+// A slot index, in a byte while that holds it.
+template <bool WIDE> struct AncOf { using type = uint8_t; };
+template <> struct AncOf<true> { using type = uint16_t; };
+
 // W: words of a row (directed: out-half, then in-half); a wave holds NT tiles
 // of 16 slots; SW waves split the slots, UW the target tiles.
 // MINW: waves per SIMD the registers are held to, four where that costs no
@@ -216,20 +234,24 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
     __shared__ uint32_t s_red[2][NWV];
     __shared__ unsigned long long s_red64[NWV];
     __shared__ int s_item, s_neq, s_nw[2];
+    __shared__ uint32_t s_gone[WU], s_rm[WU];   // vertices, positions that leave
     __shared__ int s_sumV[2];
     __shared__ uint32_t s_min[2];
     char *lds = reinterpret_cast<char *>(s_dyn);
-    uint32_t *s_rows = reinterpret_cast<uint32_t *>(lds + L.rows);   // [NA][W][urs]
+    uint32_t *s_rows = reinterpret_cast<uint32_t *>(lds + L.rows);   // [NA][W][urs], by position
     float *s_lc = reinterpret_cast<float *>(lds + L.lc);             // label cost of u (FAST: float, else int bits)
     int *s_lci = reinterpret_cast<int *>(lds + L.lc);
     int *s_l1 = reinterpret_cast<int *>(lds + L.l1);                 // vertex labels of g1, g2
     int *s_l2 = reinterpret_cast<int *>(lds + L.l2);
     uint32_t *s_r1 = reinterpret_cast<uint32_t *>(lds + L.r1);       // [2][ND * NA][W1] row of v_i, by level parity
-    uint32_t *s_img = reinterpret_cast<uint32_t *>(lds + L.img);     // [W][KP]; bits >= n2 set: never free
+    uint16_t *s_act = reinterpret_cast<uint16_t *>(lds + L.act);     // target vertex of a position (nact of them, ascending)
+    uint32_t *s_img = reinterpret_cast<uint32_t *>(lds + L.img);     // [W][KP]
+    uint32_t *s_use = reinterpret_cast<uint32_t *>(lds + L.use);     // [WU][KP] Img by position (past nact: used)
     uint32_t *s_phi = reinterpret_cast<uint32_t *>(lds + L.phi);     // [NA][W][KP] the window's part of Phi
     uint32_t *s_le = reinterpret_cast<uint32_t *>(lds + L.le);       // [WU + 1][KP] children at most T (last: deletion)
     uint32_t *s_lt = reinterpret_cast<uint32_t *>(lds + L.lt);       // ... below T
-    uint16_t *s_anc = reinterpret_cast<uint16_t *>(lds + L.anc);     // [blocks][KS]
+    using Anc = typename AncOf<(KS > 256)>::type;
+    Anc *s_anc = reinterpret_cast<Anc *>(lds + L.anc);               // [blocks][KS]
     uint16_t *s_cur = reinterpret_cast<uint16_t *>(lds + L.cur);     // [BL][KS]
     uint16_t *s_com = reinterpret_cast<uint16_t *>(lds + L.com);     // common mapping
     uint16_t *s_nbr = reinterpret_cast<uint16_t *>(lds + L.nbr);     // window neighbours of v_i (bit 15: in-arc)
@@ -285,8 +307,10 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
         for (int x = t; x < ND * NA * W1; x += T) s_r1[x] = source_word(0, x);
         for (int x = t; x < W * KP; x += T) {
             const int kk = x / KP;
-            s_img[x] = kk < WU ? ~below(n2, kk) : 0u;
+            s_img[x] = 0u;
+            if (kk < WU) s_use[x] = ~below(n2, kk);
         }
+        for (int x = t; x < URS; x += T) s_act[x] = (uint16_t)x;
         for (int x = t; x < NA * W * KP; x += T) s_phi[x] = 0u;
         for (int x = t; x < (WU + 1) * KP; x += T) {
             s_le[x] = 0u;
@@ -302,8 +326,9 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
             s_sumV[0] = s_sumV[1] = 0;
             s_min[0] = s_min[1] = 0xffffffffu;
         }
-        int nb = 1, m0 = 0, V = n2 + 1;
+        int nb = 1, m0 = 0, V = n2 + 1, nact = n2;
         int b0 = 0, nblk = 0;       // window blocks [b0, nblk)
+        int cb = 0;                 // blocks whose images have left the positions
         int dlt = 0, spr = 0;       // last level's T - m0, T - least child
         long long ce = 0;
         __syncthreads();
@@ -319,10 +344,11 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
 #pragma unroll
             for (int k = 0; k < W; ++k) im[k] = s_img[k * KP + s];
             int e = 0;
-            for (int u = part; u < n2; u += PARTS) {
+            for (int at = part; at < n2; at += PARTS) {
+                const int u = s_act[at];
                 if (!((s_img[(u >> 5) * KP + s] >> (u & 31)) & 1u)) continue;
 #pragma unroll
-                for (int k = 0; k < W; ++k) e += __popc(im[k] & s_rows[k * URS + u]);
+                for (int k = 0; k < W; ++k) e += __popc(im[k] & s_rows[k * URS + at]);
             }
 #pragma unroll
             for (int o = 1; o < PARTS; o <<= 1) e += __shfl_xor(e, o);
@@ -393,7 +419,7 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
                 }
             }
             for (int u = t; u < URS; u += T) {
-                const int lc = (u < n2 && lab1 != s_l2[u]) ? c.vsub : 0;
+                const int lc = (u < nact && lab1 != s_l2[u]) ? c.vsub : 0;
                 if (FAST) s_lc[u] = (float)lc;
                 else s_lci[u] = lc;
             }
@@ -452,23 +478,23 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
                 unsigned long long bk = ~0ull;
                 if (us < nb) {
                     const int e0 = inside(us, part) / 2, ns = s_nsub[us];
-                    for (int u = part; u <= n2; u += PARTS) {
+                    for (int at = part; at <= nact; at += PARTS) {
                         int d = s_ped[us], left = g2.m - e0, used = ns;
-                        if (u < n2) {
-                            if ((s_img[(u >> 5) * KP + us] >> (u & 31)) & 1u) continue;
+                        if (at < nact) {
+                            if ((s_use[(at >> 5) * KP + us] >> (at & 31)) & 1u) continue;
                             int kept = 0, inimg = 0, relab = 0;
                             for (int k = 0; k < W; ++k) {
-                                const uint32_t row = s_rows[k * URS + u];
+                                const uint32_t row = s_rows[k * URS + at];
                                 const uint32_t ph = s_phi[k * KP + us] | s_pc[k];
                                 kept += __popc(ph & row);
                                 inimg += __popc(s_img[k * KP + us] & row);
                                 if (LAB) {
-                                    const uint32_t f0 = (s_phi[(W + k) * KP + us] | s_pc[W + k]) ^ s_rows[(W + k) * URS + u];
-                                    const uint32_t f1 = (s_phi[(2 * W + k) * KP + us] | s_pc[2 * W + k]) ^ s_rows[(2 * W + k) * URS + u];
+                                    const uint32_t f0 = (s_phi[(W + k) * KP + us] | s_pc[W + k]) ^ s_rows[(W + k) * URS + at];
+                                    const uint32_t f1 = (s_phi[(2 * W + k) * KP + us] | s_pc[2 * W + k]) ^ s_rows[(2 * W + k) * URS + at];
                                     relab += __popc(ph & row & (f0 | f1));
                                 }
                             }
-                            d += (FAST ? (int)s_lc[u] : s_lci[u]) + c.edel * (degP - kept) + c.eins * (inimg - kept) +
+                            d += (lab1 != s_l2[at] ? c.vsub : 0) + c.edel * (degP - kept) + c.eins * (inimg - kept) +
                                  c.esub * relab;
                             left -= inimg;
                             ++used;
@@ -477,7 +503,7 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
                         }
                         const int total = d + c.vins * (n2 - used) + c.eins * left;
                         const unsigned long long key = ((unsigned long long)(unsigned)total << 32) |
-                                                       (unsigned)((us << 10) | u);
+                                                       (unsigned)((us << 10) | at);
                         bk = key < bk ? key : bk;
                     }
                 }
@@ -489,7 +515,7 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
 #pragma unroll
                     for (int k = 1; k < NWV; ++k) m = s_red64[k] < m ? s_red64[k] : m;
                     const int low = (int)(m & 0xffffffffu);
-                    s_sel[0] = (low & 1023) == n2 ? (low | DELU) : low;
+                    s_sel[0] = (low & 1023) == nact ? (low | DELU) : low;
                 }
                 nb_new = 1;
             } else {
@@ -499,7 +525,7 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
                     for (int x = t; x < (WU + 1) * KS; x += T) {
                         const int k = x / KS, s = x % KS;
                         if (s < nb) {
-                            const uint32_t m = k < WU ? ~s_img[k * KP + s] : 1u;
+                            const uint32_t m = k < WU ? ~s_use[k * KP + s] : 1u;
                             s_le[k * KP + s] = m;
                             s_lt[k * KP + s] = m;
                         }
@@ -566,8 +592,8 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
                         spread_row(1u << col, e_lo);
                         // (opaque, so that the tiles' bounds are compared where
                         // they are needed and not kept for the whole pair)
-                        int n2v = __builtin_amdgcn_readfirstlane(n2), qv = q;
-                        asm volatile("" : "+s"(n2v), "+v"(qv));
+                        int nav = __builtin_amdgcn_readfirstlane(nact), qv = q;
+                        asm volatile("" : "+s"(nav), "+v"(qv));
                         constexpr int TG = 8 / UW;           // tiles of a 128-vertex group
                         constexpr int TP = TG >= 4 && W == 16 ? 4 : (TG > 1 ? 2 : 1);   // tiles in flight
 #pragma unroll
@@ -575,14 +601,14 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
                             uint32_t bd[NT][4];
 #pragma unroll
                             for (int n = 0; n < NT; ++n)
-                                spread_one(s_img[(4 * g + qv) * KP + (sw * NT + n) * 16 + col], bd[n]);
+                                spread_one(4 * g + qv < WU ? s_use[(4 * g + qv) * KP + (sw * NT + n) * 16 + col] : 0u, bd[n]);
 #pragma unroll
                             for (int kk = 0; kk < TG; kk += TP) {
                                 const int k0 = g * TG + kk;   // this wave's tiles k0 .. k0 + TP - 1
                                 if (k0 >= NTL) continue;
                                 // a few tiles' operands at a time
                                 __builtin_amdgcn_sched_barrier(0);
-                                if (16 * (k0 * UW + uw) >= n2v) {
+                                if (16 * (k0 * UW + uw) >= nav) {
 #pragma unroll
                                     for (int h = 0; h < TP; ++h)
 #pragma unroll
@@ -667,9 +693,14 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
                                         if (k0 + h >= NTL) continue;
                                         uint32_t w = 0u;
                                         if (FAST) {
-                                            const v4f y = dd[h][n];
+                                            // (med3: fminf of a matrix result costs a second
+                                            // instruction, which quiets a NaN that cannot be)
+                                            float y[4];
 #pragma unroll
-                                            for (int r = 0; r < 4; ++r) w = __builtin_amdgcn_cvt_pk_u8_f32(fminf(y[r], (float)XCAP), r, w);
+                                            for (int r = 0; r < 4; ++r) {
+                                                y[r] = __builtin_amdgcn_fmed3f(dd[h][n][r], -1.f, (float)XCAP);
+                                                w = __builtin_amdgcn_cvt_pk_u8_f32(y[r], r, w);
+                                            }
                                             yminf = fminf(yminf, fminf(fminf(y[0], y[1]), fminf(y[2], y[3])));
                                         } else {
                                             const bool dead = (sw * NT + n) * 16 + col >= nb;
@@ -709,7 +740,7 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
                                 else ymini = min(ymini, y);
                             }
                         }
-                        int ylow;   // lower bound of the least byte (exact when sh = 0)
+                        int ylow;   // lower bound of the least byte (exact when sh = 0 and not below 0)
                         {
                             const int yl = FAST ? (int)floorf(fminf(yminf, 1.0e6f)) : min(ymini >> sh, 1000000);
                             const uint32_t wm = wave_umin((uint32_t)yl + 0x40000000u);
@@ -730,12 +761,21 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
                             const uint32_t Ca = ((uint32_t)ta * 0x01010101u) | HI, Cb = ((uint32_t)tc * 0x01010101u) | HI;
                             uint32_t ca = 0u, cb = 0u;
 #pragma unroll
-                            for (int n = 0; n < NT; ++n)
+                            for (int k8 = 0; k8 < NTL; k8 += 8) {
+                                if (k8 > 0 && 16 * k8 * UW >= nact) break;   // past the last tile
 #pragma unroll
-                                for (int k = 0; k < NCAND; ++k) {
-                                    ca += (uint32_t)__popc((Ca - cand[n][k]) & HI);
-                                    cb += (uint32_t)__popc((Cb - cand[n][k]) & HI);
-                                }
+                                for (int n = 0; n < NT; ++n)
+#pragma unroll
+                                    for (int k = k8; k < k8 + 8 && k < NTL; ++k) {
+                                        ca += (uint32_t)__popc((Ca - cand[n][k]) & HI);
+                                        cb += (uint32_t)__popc((Cb - cand[n][k]) & HI);
+                                    }
+                            }
+#pragma unroll
+                            for (int n = 0; n < NT; ++n) {
+                                ca += (uint32_t)__popc((Ca - cand[n][NTL]) & HI);
+                                cb += (uint32_t)__popc((Cb - cand[n][NTL]) & HI);
+                            }
                             const uint32_t w = wave_sum(ca | (cb << 16));
                             if (lane == 0) s_red[par][wid] = w;
                             __syncthreads();
@@ -795,6 +835,7 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
                         const int slot = (sw * NT + n) * 16 + col;
 #pragma unroll
                         for (int k4 = 0; k4 < NCAND; k4 += 4) {
+                            if (k4 > 0 && k4 + 4 <= NTL && 16 * k4 * UW >= nact) continue;
                             // most words hold no survivor: one test for four
                             uint32_t f[4], any = 0u;
 #pragma unroll
@@ -871,33 +912,38 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
             // ---------------- update: the new slots gather their parents' state ...
             const int par = i & 1;
             const bool live = us < nb_new;
-            int p = 0, u = DELU, nped = 0, nns = 0;
-            uint32_t nim[NWP];
+            int p = 0, at = DELU, nped = 0, nns = 0;
+            uint32_t nim[NWP], nus[NWP];
             uint16_t cv[(BL + PARTS - 1) / PARTS];
             const int r8 = i % BL;      // row of this level in its block
             if (live) {
                 const int sel = s_sel[us];
                 p = sel >> 10;
-                u = sel & 1023;
+                at = sel & 1023;
             }
-            const bool sub = u < n2;
+            const bool sub = at < nact;
+            const int u = sub ? (int)s_act[at] : n2;
             {
                 int kept = 0, inimg = 0, relab = 0;
 #pragma unroll
                 for (int k = 0; k < NWP; ++k) {
                     const int w = part + k * PARTS;
-                    nim[k] = 0u;
+                    nim[k] = nus[k] = 0u;
+                    if (w < WU && live) {
+                        nus[k] = s_use[w * KP + p];
+                        if (sub && w == (at >> 5)) nus[k] |= 1u << (at & 31);
+                    }
                     if (w < W && live) {
                         const uint32_t im = s_img[w * KP + p];
                         nim[k] = im;
                         if (sub) {
-                            const uint32_t row = s_rows[w * URS + u];
+                            const uint32_t row = s_rows[w * URS + at];
                             const uint32_t ph = s_phi[w * KP + p] | s_pc[w];
                             kept += __popc(ph & row);
                             inimg += __popc(im & row);
                             if (LAB) {
-                                const uint32_t f0 = (s_phi[(W + w) * KP + p] | s_pc[W + w]) ^ s_rows[(W + w) * URS + u];
-                                const uint32_t f1 = (s_phi[(2 * W + w) * KP + p] | s_pc[2 * W + w]) ^ s_rows[(2 * W + w) * URS + u];
+                                const uint32_t f0 = (s_phi[(W + w) * KP + p] | s_pc[W + w]) ^ s_rows[(W + w) * URS + at];
+                                const uint32_t f1 = (s_phi[(2 * W + w) * KP + p] | s_pc[2 * W + w]) ^ s_rows[(2 * W + w) * URS + at];
                                 relab += __popc(ph & row & (f0 | f1));
                             }
                             if (w == (u >> 5) || (DIR && w == (u >> 5) + WU)) nim[k] |= 1u << (u & 31);
@@ -914,7 +960,7 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
                     nped = s_ped[p];
                     nns = s_nsub[p] + (sub ? 1 : 0);
                     if (sub)
-                        nped += (FAST ? (int)s_lc[u] : s_lci[u]) + c.edel * (degP - kept) + c.eins * (inimg - kept) +
+                        nped += (lab1 != s_l2[at] ? c.vsub : 0) + c.edel * (degP - kept) + c.eins * (inimg - kept) +
                                 c.esub * relab;
                     else
                         nped += del_cost;
@@ -932,20 +978,23 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
                 }
             }
             // ... and write it, all at once (the ancestor rows in steps)
-            uint16_t av[MAXA];
+            Anc av[MAXA];
             bool rest = true;
             for (int g = b0; rest; g += MAXA * PARTS) {
 #pragma unroll
                 for (int k = 0; k < MAXA; ++k) {
                     const int r = g + part + k * PARTS;
-                    av[k] = (r < nblk && live) ? s_anc[r * KS + p] : (uint16_t)0;
+                    av[k] = (r < nblk && live) ? s_anc[r * KS + p] : (Anc)0;
                 }
                 __syncthreads();
                 if (g == b0) {
                     if (live) {
 #pragma unroll
-                        for (int k = 0; k < NWP; ++k)
-                            if (part + k * PARTS < W) s_img[(part + k * PARTS) * KP + us] = nim[k];
+                        for (int k = 0; k < NWP; ++k) {
+                            const int w = part + k * PARTS;
+                            if (w < W) s_img[w * KP + us] = nim[k];
+                            if (w < WU) s_use[w * KP + us] = nus[k];
+                        }
                         const uint16_t xi = sub ? (uint16_t)u : (uint16_t)DEL16;
                         const bool full = r8 == BL - 1;
 #pragma unroll
@@ -959,7 +1008,7 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
                         if (part == 0) {
                             s_ped[us] = nped;
                             s_nsub[us] = nns;
-                            if (full) s_anc[nblk * KS + us] = (uint16_t)us;
+                            if (full) s_anc[nblk * KS + us] = (Anc)us;
                         }
                     }
 #pragma unroll
@@ -996,6 +1045,94 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
             __syncthreads();
             V = s_sumV[par];
             m0 = (int)s_min[par];
+
+            // ---------------- images common to the whole beam are used in every
+            // slot: they go behind the other positions, and every slot's bits
+            // close up (CB blocks at a time: fewer would free no group of tiles;
+            // not for the last levels, where it would cost more than it saves)
+            if (b0 - cb >= CB && i + 2 * BL < n1) {
+                if (t < WU) s_gone[t] = 0u;
+                __syncthreads();
+                for (int x = BL * cb + t; x < BL * b0; x += T) {
+                    const uint32_t v = s_com[x];
+                    if (v != DEL16) atomicOr(&s_gone[v >> 5], 1u << (v & 31));
+                }
+                __syncthreads();
+                constexpr int AE = (32 * WU + T - 1) / T;   // positions of a thread
+                uint16_t ua[AE];
+                int lb[AE], to[AE];
+#pragma unroll
+                for (int k = 0; k < AE; ++k) {
+                    const int x = t + k * T;
+                    ua[k] = 0;
+                    lb[k] = 0;
+                    if (x < nact) {
+                        ua[k] = s_act[x];
+                        lb[k] = s_l2[x];
+                    }
+                    const unsigned long long m =
+                        __ballot(x < nact && ((s_gone[ua[k] >> 5] >> (ua[k] & 31)) & 1u));
+                    if ((lane & 31) == 0 && x < 32 * WU) s_rm[x >> 5] = (uint32_t)(lane ? m >> 32 : m);
+                }
+                __syncthreads();
+                int out = 0;
+#pragma unroll
+                for (int w = 0; w < WU; ++w) out += __popc(s_rm[w]);
+#pragma unroll
+                for (int k = 0; k < AE; ++k) {
+                    const int x = t + k * T;
+                    int before = 0;
+#pragma unroll
+                    for (int w = 0; w < WU; ++w) before += __popc(s_rm[w] & below(x, w));
+                    const bool leaves = x < nact && ((s_rm[x >> 5] >> (x & 31)) & 1u);
+                    to[k] = leaves ? nact - out + before : x - before;
+                    if (x < nact) {
+                        s_act[to[k]] = ua[k];
+                        s_l2[to[k]] = lb[k];
+                    }
+                }
+#pragma unroll 1
+                for (int r = 0; r < NA * W; r += 4) {
+                    uint32_t rv[AE][4];
+#pragma unroll
+                    for (int k = 0; k < AE; ++k)
+#pragma unroll
+                        for (int z = 0; z < 4; ++z) rv[k][z] = t + k * T < nact ? s_rows[(r + z) * URS + t + k * T] : 0u;
+                    __syncthreads();
+#pragma unroll
+                    for (int k = 0; k < AE; ++k)
+#pragma unroll
+                        for (int z = 0; z < 4; ++z)
+                            if (t + k * T < nact) s_rows[(r + z) * URS + to[k]] = rv[k][z];
+                }
+                // one thread a slot: positions taken out from the highest on, a
+                // used one shifted in at the top
+                if (t < KS) {
+                    uint32_t wv[WU];
+#pragma unroll
+                    for (int k = 0; k < WU; ++k) wv[k] = s_use[k * KP + t];
+#pragma unroll
+                    for (int w = WU - 1; w >= 0; --w) {
+                        uint32_t m = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_rm[w]);
+                        while (m) {
+                            const int b = 31 - __builtin_clz(m);
+                            m ^= 1u << b;
+                            const uint32_t low = (1u << b) - 1u;   // bits that stay
+#pragma unroll
+                            for (int k = w; k < WU; ++k) {
+                                const uint32_t up = k + 1 < WU ? wv[k + 1 < WU ? k + 1 : 0] : 0xffffffffu;
+                                const uint32_t sh = (wv[k] >> 1) | (up << 31);
+                                wv[k] = k == w ? (wv[k] & low) | (sh & ~low) : sh;
+                            }
+                        }
+                    }
+#pragma unroll
+                    for (int k = 0; k < WU; ++k) s_use[k * KP + t] = wv[k];
+                }
+                nact -= out;
+                cb = b0;
+                __syncthreads();
+            }
         }
 
         // ---------------- completion: insert what is left of g2, pick the best leaf

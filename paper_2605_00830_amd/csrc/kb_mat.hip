@@ -55,7 +55,7 @@ int slots_of(const MatConfig &m) { return 16 * m.NT * m.SW; }
 
 int lds_bytes(const BlockShape &s, const MatConfig &m) {
     const int KS = slots_of(m), blocks = (std::max(s.nmax1, 1) + BL - 1) / BL;
-    return mat_lds(m.W, KS, s.PL > 0 ? 3 : 1, s.directed ? 2 : 1).anc + blocks * KS * 2;
+    return mat_lds(m.W, KS, s.PL > 0 ? 3 : 1, s.directed ? 2 : 1).anc + blocks * KS * (KS > 256 ? 2 : 1);
 }
 
 constexpr int kMatLdsBytes = 158 * 1024;

@@ -298,7 +298,7 @@ __global__ __launch_bounds__(WT) void wm_expand(Ctx c, int i, int chunks, int gr
     tile.score(c, sl, s0, B, u0, shift, [&](int, const v4f &y) {
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            if (y[r] < 8388608.f) atomicAdd(&s_hist[(int)(over ? fminf(y[r], top) : y[r])], 1u);
+            if (y[r] < 8388608.f) atomicAdd(&s_hist[(int)(over ? __builtin_amdgcn_fmed3f(y[r], 0.f, top) : y[r])], 1u);
     });
     // the deletions: one per slot, from the first k-group's lanes
     if (chunk == 0 && (t & 63) < 16 && s0 + (uint32_t)((t >> 6) * 16 + (t & 15)) < B) {
@@ -464,7 +464,7 @@ __global__ __launch_bounds__(WT) void wm_mark(Ctx c, int i, int chunks, int grou
         tile.score(c, sl, s0, B, u0, shift, [&](int k, const v4f &y) {
             uint32_t w = 0u;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) w = __builtin_amdgcn_cvt_pk_u8_f32(fminf(y[r], (float)XCAP), r, w);
+            for (int r = 0; r < 4; ++r) w = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(y[r], 0.f, (float)XCAP), r, w);
             const uint32_t fle = (0x81818181u - w) & HI;
             if (fle) {
                 const uint32_t flt = (0x80808080u - w) & HI;

@@ -98,3 +98,18 @@ def test_long_windows(ged):
     er = [graph(208, k, m, 0.2, 0) for k, m in enumerate([200, 30])]
     for K in (16, 64, 256):
         check(ged, [path, none] + er, [[0, 0], [1, 1], [0, 1], [1, 0], [2, 3]], UNIT, K)
+
+
+@pytest.mark.parametrize("n2", [40, 63, 64, 65, 127, 128, 200, 256, 300])
+@pytest.mark.parametrize("K", [1, 12, 32, 64])
+def test_common_images(ged, n2, K):
+    """Long sources and narrow beams: images common to the whole beam leave the target's positions several
+    times, down to none left, with one row a vertex, label planes, directed halves and a completed last level."""
+    gs = [graph(209, k, n, 0.1, 0) for k, n in enumerate([130, 200])] + [graph(210, 0, n2, 0.1, 0)]
+    check(ged, gs, [[0, 2], [1, 2]], PAPER, K, complete=K == 12)
+    check(ged, gs, [[0, 2]], (900_001, 800_003, 700_001, 30_011, 20_021, 35_003), K, complete=K == 64)
+    if n2 <= 256:
+        gs = [graph(211, 0, 150, 0.1, 3), graph(211, 1, n2, 0.1, 3)]
+        check(ged, gs, [[0, 1]], PAPER, K)
+        ds = [graph(212, 0, 140, 0.05, 3, True), graph(212, 1, n2, 0.05, 3, True)]
+        check(ged, ds, [[0, 1]], PAPER, K, directed=True, complete=K == 32)
