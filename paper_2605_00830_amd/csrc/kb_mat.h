@@ -56,8 +56,8 @@
 // no level for it, 746 -> 740.)
 //
 // Measured against the candidate-matrix kernel of kb_block.hip (same box, us
-// a launch): 256 pairs of 100..500 vertices at K = 256 81,900 -> 12,560; 512
-// pairs of 65..250 at K = 64 9,290 -> 2,060; and before the positions closed up
+// a launch): 256 pairs of 100..500 vertices at K = 256 81,900 -> 12,380; 512
+// pairs of 65..250 at K = 64 9,290 -> 1,870; and before the positions closed up
 // 400 pairs of 65..128 at K = 1024 20,034 -> 6,379; 100 labelled pairs of
 // 300..500 at K = 64 131,104 -> 12,191; 200 labelled directed pairs of 130..250
 // at K = 80 41,755 -> 5,939.  A launch lasts as long as its largest pair.  A
@@ -226,7 +226,10 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
     constexpr int NOP = LAB ? (FAST ? 5 : 6) : NS; // ... with four label codes after them
     constexpr int NCAND = NTL + 1;              // words of a slot tile: target tiles, then the deletion
     constexpr int NWP = (W + PARTS - 1) / PARTS;
-    constexpr int MAXA = 16;                    // ancestor rows a thread moves per step
+    // ancestor rows a thread moves per step: 16 a slot cover most windows (mean 3.5
+    // blocks at K = 64, 9 at 256), and each further one is code that finds no row
+    // (16 a thread instead: 512 pairs of 65..250, K = 64, 2,026 against 1,862 us)
+    constexpr int MAXA = PARTS >= 4 ? 4 : 16 / PARTS;
     static_assert(W % 4 == 0 && KS <= T && 8 % UW == 0 && (2 * WU) % UW == 0, "shape");
 
     constexpr MatLds L = mat_lds(W, KS, NA, ND);
