@@ -199,6 +199,19 @@ __device__ __forceinline__ unsigned long long wave_min64(unsigned long long v) {
     return v;
 }
 
+// Sum over the N neighbouring lanes of a slot, in each of them (N a power of two,
+// at most a row of 16): DPP within a quad, then the mirrors, whose lanes hold
+// the other half's sum.  (Lane shuffles go through LDS, one round trip a step.)
+template <int N>
+__device__ __forceinline__ uint32_t parts_sum(uint32_t v) {
+    static_assert(N == 1 || N == 2 || N == 4 || N == 8 || N == 16, "lanes of a slot");
+    if (N > 1) v += dpp_ror<0xb1>(v);    // quad_perm 1 0 3 2
+    if (N > 2) v += dpp_ror<0x4e>(v);    // quad_perm 2 3 0 1
+    if (N > 4) v += dpp_ror<0x141>(v);   // row_half_mirror
+    if (N > 8) v += dpp_ror<0x140>(v);   // row_mirror
+    return v;
+}
+
 // A slot index, in a byte while that holds it.
 template <bool WIDE> struct AncOf { using type = uint8_t; };
 template <> struct AncOf<true> { using type = uint16_t; };
@@ -346,16 +359,14 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
             uint32_t im[W];
 #pragma unroll
             for (int k = 0; k < W; ++k) im[k] = s_img[k * KP + s];
-            int e = 0;
+            uint32_t e = 0;
             for (int at = part; at < n2; at += PARTS) {
                 const int u = s_act[at];
                 if (!((s_img[(u >> 5) * KP + s] >> (u & 31)) & 1u)) continue;
 #pragma unroll
-                for (int k = 0; k < W; ++k) e += __popc(im[k] & s_rows[k * URS + at]);
+                for (int k = 0; k < W; ++k) e += (uint32_t)__popc(im[k] & s_rows[k * URS + at]);
             }
-#pragma unroll
-            for (int o = 1; o < PARTS; o <<= 1) e += __shfl_xor(e, o);
-            return e;
+            return (int)parts_sum<PARTS>(e);
         };
 
         for (int i = 0; i < n1; ++i) {
@@ -953,12 +964,11 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
                         }
                     }
                 }
-#pragma unroll
-                for (int o = 1; o < PARTS; o <<= 1) {
-                    kept += __shfl_xor(kept, o);
-                    inimg += __shfl_xor(inimg, o);
-                    if (LAB) relab += __shfl_xor(relab, o);
-                }
+                // (none of the three reaches 1024)
+                const uint32_t sum = parts_sum<PARTS>((uint32_t)(kept | (inimg << 10) | (relab << 20)));
+                kept = (int)(sum & 1023u);
+                inimg = (int)((sum >> 10) & 1023u);
+                relab = (int)(sum >> 20);
                 if (live) {
                     nped = s_ped[p];
                     nns = s_nsub[p] + (sub ? 1 : 0);
