@@ -65,7 +65,8 @@ def ops_per_candidate(w: int, planes: int) -> int:
 KERNEL_SOURCES = {"kb_wave_kernel": ("kb_wave.hip", "wave_common.h", "ged_types.h"),
                   "kb_wave2_kernel": ("kb_wave2.h", "kb_wave2.hip", "kb_wave2_k128.hip", "kb_wave2_src128.hip",
                                       "wave_common.h", "ged_types.h", "ged_internal.h", "include/ged.h"),
-                  "kb_block_kernel": ("kb_block.hip", "ged_internal.h", "ged_types.h", "include/ged.h")}
+                  "kb_block_kernel": ("kb_mat.h", "kb_mat.hip", "kb_block.hip", "wave_common.h", "ged_internal.h",
+                                      "ged_types.h", "include/ged.h")}
 
 
 def kernel_source_hash(kernel: str) -> str:
@@ -315,8 +316,7 @@ def large_k_measure(ged, reps: int = 5, cpu: bool = True):
     `reps` timed runs (HIP events on the launch stream) after one warm-up run; parity
     with the oracle's stored result where there is one; the roofline of a run: its
     children at ops_per_candidate(target words, planes) each over its duration against
-    the int32 VALU peak, and its candidate-matrix bytes (each child's PED written once
-    and read back by the count and compaction passes, 12 B) against HBM bandwidth."""
+    the int32 VALU peak."""
     import torch
     from paper_2605_00830_amd import synth
     stored = json.load(open(LARGE_K_ORACLE)) if os.path.exists(LARGE_K_ORACLE) else {}
@@ -350,9 +350,7 @@ def large_k_measure(ged, reps: int = 5, cpu: bool = True):
                  "ratio_to_paper_a100": round(paper_ms / ms, 1),
                  "roofline": {"bound": "alu", "achieved": round(ach, 4), "peak": round(PEAK_INT32_TOPS, 2),
                               "unit": "Tops/s", "frac": round(ach / PEAK_INT32_TOPS, 5),
-                              "ops_per_child": ops_per_candidate(words, 0),
-                              "candidate_bytes_gbps": round(12.0 * ce / (ms / 1e3) / 1e9, 1),
-                              "candidate_bytes_frac_of_hbm": round(12.0 * ce / (ms / 1e3) / 8.0e12, 5)}}
+                              "ops_per_child": ops_per_candidate(words, 0)}}
         ref = stored.get(f"{w.name}@K{K}")
         if ref is not None:
             entry["parity"] = {"oracle": "tests/golden/large_k.json",

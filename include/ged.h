@@ -414,9 +414,9 @@ ged_status ged_edit_path(ged_db *db, const ged_pair *h_pairs, int64_t npairs, ge
  * Single-pair search at large K (the paper's own regime, Sec. 5: K from
  * thousands to 1.2 million).  The whole device works on one pair: the beam
  * lives in device memory, and every level of Alg. 1 is a sequence of
- * grid-wide kernels -- every child's PED (Sec. 2.3) into a candidate matrix
- * with a histogram of the PEDs, the K-th smallest child by histogram select
- * (refined where the PED range needs it), stable compaction of the survivors
+ * grid-wide kernels -- every child's PED (Sec. 2.3) and a histogram of the
+ * PEDs, the K-th smallest child by histogram select (refined where the PED
+ * range needs it), stable compaction of the survivors
  * in generation order, and the beam update.  The result is the same as the
  * batched search's (ged_plan_run) at the same K, bit for bit.
  *
