@@ -56,8 +56,8 @@
 // no level for it, 746 -> 740.)
 //
 // Measured against the candidate-matrix kernel of kb_block.hip (same box, us
-// a launch): 256 pairs of 100..500 vertices at K = 256 81,900 -> 12,380; 512
-// pairs of 65..250 at K = 64 9,290 -> 1,870; and before the positions closed up
+// a launch): 256 pairs of 100..500 vertices at K = 256 80,050 -> 12,350; 512
+// pairs of 65..250 at K = 64 9,220 -> 1,810; and before the positions closed up
 // 400 pairs of 65..128 at K = 1024 20,034 -> 6,379; 100 labelled pairs of
 // 300..500 at K = 64 131,104 -> 12,191; 200 labelled directed pairs of 130..250
 // at K = 80 41,755 -> 5,939.  A launch lasts as long as its largest pair.  A
