@@ -756,7 +756,10 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
                         }
                         int ylow;   // lower bound of the least byte (exact when sh = 0 and not below 0)
                         {
-                            const int yl = FAST ? (int)floorf(fminf(yminf, 1.0e6f)) : min(ymini >> sh, 1000000);
+                            // (held to 2^30 on both sides, so that its offset below cannot wrap: a child
+                            // may lie up to 2^31 below b, and anything below 0 says the same)
+                            const int yl = FAST ? (int)floorf(fminf(yminf, 1.0e6f))
+                                                : max(min(ymini >> sh, 1000000), -0x40000000);
                             const uint32_t wm = wave_umin((uint32_t)yl + 0x40000000u);
                             if (lane == 0) s_red[0][wid] = wm;
                             __syncthreads();
