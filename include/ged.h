@@ -423,7 +423,7 @@ ged_status ged_edit_path(ged_db *db, const ged_pair *h_pairs, int64_t npairs, ge
  * ged_wide_create sizes and allocates the workspace for pair (src, dst) of
  * `db` at beam width K (1 <= K <= GED_MAX_K_WIDE): about
  * K * (4 (n2 + 1) + 4 n1 + 24 + 4 w2 (3 + planes)) bytes (w2 = target words
- * of 32 vertices).  ged_wide_bytes returns what it holds.  ged_wide_run
+ * of 32 vertices), and at least about 17 MB.  ged_wide_bytes returns what it holds.  ged_wide_run
  * enqueues the search on `stream` (NULL = the null stream); outputs are
  * device pointers: d_dist[0] the distance, d_map[0..n1) the target vertex
  * of each source vertex (-1 = deleted), d_cand[0] (may be NULL) the children

@@ -12,10 +12,12 @@
 //   expand   Phi of the 64 slots (stored for the others), every child's PED,
 //            an LDS histogram above the least parent PED, added to one of HC
 //            copies (atomics on one address are serialised, about 10 ns each).
+//            A workgroup with children past the histogram's range (HB values)
+//            scores them again, HB values at a time, into the far histogram:
+//            exact counts of every value, and their sums per HB of them.
 //   mark     the threshold T from the histogram, by every workgroup (should
-//            the K-th child lie past the histogram's range -- the host admits
-//            only costs whose levels stay well inside -- the children are
-//            counted there, exactly); then scores again -- cheaper than a
+//            the K-th child lie past its range: from the far one, first the
+//            sums, then one group's values); then scores again -- cheaper than a
 //            candidate matrix of 4 bytes a child, written once and read twice --
 //            and stores, per slot, a bit per vertex for children at most T and
 //            below T, and their counts per 64 slots.
@@ -44,6 +46,8 @@ constexpr int WT = 256;
 constexpr int NWV = WT / 64;
 constexpr int HB = 4096;          // histogram bins; the last one also counts what is above
 constexpr int HC = 2;             // copies
+constexpr uint32_t FAR = (uint32_t)kFastBound;   // values of the far histogram (no PED of the search reaches it)
+constexpr int FC = (int)(FAR / HB);              // ... and sums of HB of them
 constexpr int GS = 64;            // slots of a workgroup
 constexpr int GP = GS + 16;       // their LDS stride
 constexpr int CT = 8;             // target tiles of a workgroup (128 vertices)
@@ -58,7 +62,8 @@ struct Level {
     uint32_t B, m0, mmax;    // parents, their least and largest PED
     uint32_t quota;          // children equal to the threshold that survive
     uint32_t b0;             // first block not yet common
-    uint32_t pad[3];
+    uint32_t far;            // the level has children past the histogram
+    uint32_t pad[2];
 };
 
 // What a level needs of v_i and the common mapping, made while the level before
@@ -94,6 +99,7 @@ struct Ctx {
     uint32_t *cnt;           // [2][groups] below T, equal to T per 64 slots
     uint32_t *rec;           // [Kp]
     uint32_t *hist;          // [HC][HB]
+    uint32_t *far, *farc;    // [FAR] children past the histogram, by value above the least parent PED; [FC] sums
     Level *st;
     Prep *prep;
     unsigned long long *ce, *best;   // best: a key per workgroup
@@ -134,6 +140,11 @@ __global__ __launch_bounds__(WT) void wm_init(Ctx c) {
         c.st[l] = s;
     }
     for (int b = t; b < HC * HB; b += T) c.hist[b] = 0u;
+    if (c.pedmax >= (uint32_t)(HB - 1)) {   // (else no level has values past the histogram)
+        const uint32_t end = (c.pedmax / HB + 1u) * HB;   // whole sums
+        for (uint32_t b = t; b < end; b += T) c.far[b] = 0u;
+        for (int b = t; b < FC; b += T) c.farc[b] = 0u;
+    }
     for (int k = t; k < c.w2; k += T) c.img[0][(size_t)k * c.Kp] = 0u;
     for (int k = t; k < (int)(sizeof(Prep) / 4); k += T) reinterpret_cast<uint32_t *>(c.prep)[k] = 0u;
     if (t == 0) {
@@ -184,8 +195,8 @@ struct Tile {
     // PEDs plus `shift` (used vertices and dead slots near 2^24), for the
     // chunk's tiles in turn
     template <class F>
-    __device__ __forceinline__ void score(const Ctx &c, const Slot &sl, uint32_t s0, uint32_t B, int u0, float shift, F f) const {
-        const int t = threadIdx.x, lane = t & 63, wid = __builtin_amdgcn_readfirstlane(t >> 6);
+    __device__ __forceinline__ void score(const Ctx &c, const Slot &sl, int t, uint32_t s0, uint32_t B, int u0, float shift, F f) const {
+        const int lane = t & 63, wid = __builtin_amdgcn_readfirstlane(t >> 6);
         const int q = lane >> 4, col = lane & 15, ls = wid * 16 + col;
         uint32_t Bo[KST][4], bd[4];
 #pragma unroll
@@ -244,7 +255,7 @@ template <int W>
 __global__ __launch_bounds__(WT) void wm_expand(Ctx c, int i, int chunks, int groups, int hist) {
     __shared__ uint32_t s_rows[W * RS], s_phi[W * GP];
     __shared__ __attribute__((aligned(16))) float s_lc[RS];
-    __shared__ uint32_t s_hist[HB];
+    __shared__ uint32_t s_hist[HB], s_next, s_past;
     __shared__ uint16_t s_nbr[MAXN];
     const int t = threadIdx.x, slot = t % GS, p0 = t / GS;
     constexpr int PT = WT / GS;
@@ -267,6 +278,7 @@ __global__ __launch_bounds__(WT) void wm_expand(Ctx c, int i, int chunks, int gr
     for (int x = t; x < nbins; x += WT) s_hist[x] = 0u;
     for (int x = WT + t; x < nw; x += WT) s_nbr[x] = c.prep->nbr[x];
     if (chunk == 0 && t < 2) c.cnt[t * groups + group] = 0u;
+    if (t == 0) s_past = 0u;
     __syncthreads();
     {
         const uint32_t s = min(s0 + (uint32_t)slot, B - 1u);
@@ -295,7 +307,7 @@ __global__ __launch_bounds__(WT) void wm_expand(Ctx c, int i, int chunks, int gr
 
     const float shift = (float)((int)(deg * (uint32_t)c.c.edel) - (int)m0), top = (float)(nbins - 1);
     const bool over = nbins == HB;   // children past the last bin are possible
-    tile.score(c, sl, s0, B, u0, shift, [&](int, const v4f &y) {
+    tile.score(c, sl, t, s0, B, u0, shift, [&](int, const v4f &y) {
 #pragma unroll
         for (int r = 0; r < 4; ++r)
             if (y[r] < 8388608.f) atomicAdd(&s_hist[(int)(over ? __builtin_amdgcn_fmed3f(y[r], 0.f, top) : y[r])], 1u);
@@ -307,9 +319,76 @@ __global__ __launch_bounds__(WT) void wm_expand(Ctx c, int i, int chunks, int gr
     }
     __syncthreads();
     uint32_t *out = c.hist + (size_t)(blockIdx.x % HC) * HB;
+    uint32_t near = 0u;   // children below the last bin (of HB)
     for (int b = t; b < nbins; b += WT) {
         const uint32_t h = s_hist[b];
         if (h) atomicAdd(&out[b], h);
+        near += b < HB - 1 ? h : 0u;
+    }
+    if (!over || s_hist[HB - 1] == 0u) return;
+    near = wave_sum(near);
+    if ((t & 63) == 0) atomicAdd(&s_past, near);
+    __syncthreads();
+    // children of this workgroup past the histogram: HB values from `lo` on, then
+    // from the least value above those, until there is none, or K are counted,
+    // as the K-th of all children lies among them then (the slot's words are
+    // loaded again rather than held in registers, as operands, from above on)
+    if (s_past >= c.K) return;
+    for (uint32_t lo = HB - 1;;) {
+        __syncthreads();
+        sl.load(c, i, s0, u0);
+        for (int b = t; b < HB; b += WT) s_hist[b] = 0u;
+        if (t == 0) s_next = NONE;
+        __syncthreads();
+        // (such levels have few values: the lanes that hold the first one's, then
+        // those that hold the next one's, add as one)
+        uint32_t above = NONE;
+        auto take = [&](uint32_t d, bool live) {
+            if (live && d >= lo + (uint32_t)HB) above = min(above, d);
+            bool in = live && d - lo < (uint32_t)HB;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const unsigned long long m = __ballot(in);
+                if (m == 0ull) break;
+                const int one = __builtin_ctzll(m);
+                const uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)d, one);
+                const unsigned long long same = __ballot(in && d == v);
+                if ((t & 63) == one) atomicAdd(&s_hist[v - lo], (uint32_t)__popcll(same));
+                in = in && d != v;
+            }
+            if (in) atomicAdd(&s_hist[d - lo], 1u);
+        };
+        int t2 = t;   // (opaque: nothing of a pass is formed before it and kept over the loop)
+        asm volatile("" : "+v"(t2));
+        tile.score(c, sl, t2, s0, B, u0, shift, [&](int, const v4f &y) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) take((uint32_t)(int)fminf(y[r], (float)FAR), y[r] < 8388608.f);
+        });
+        if (chunk == 0)
+            take(sl.ped - m0 + (uint32_t)c.c.vdel + deg * (uint32_t)c.c.edel,
+                 (t & 63) < 16 && s0 + (uint32_t)((t >> 6) * 16 + (t & 15)) < B);
+        above = wave_umin(above);
+        if ((t & 63) == 0 && above != NONE) atomicMin(&s_next, above);
+        __syncthreads();
+        const uint32_t next = s_next, c0 = lo / HB;   // the values' sums: c0, and c0 + 1
+        uint32_t a = 0u, b1 = 0u;
+        for (int b = t; b < HB; b += WT) {
+            const uint32_t h = s_hist[b], v = lo + (uint32_t)b;
+            if (h) atomicAdd(&c.far[v], h);   // (a child's value: below FAR)
+            a += v / HB == c0 ? h : 0u;
+            b1 += v / HB == c0 ? 0u : h;
+        }
+        a = wave_sum(a);
+        b1 = wave_sum(b1);
+        if ((t & 63) == 0) {
+            if (a) atomicAdd(&c.farc[c0], a);
+            if (b1) atomicAdd(&c.farc[c0 + 1u], b1);
+            if (a + b1) atomicAdd(&s_past, a + b1);
+        }
+        if (next == NONE) return;
+        __syncthreads();
+        if (s_past >= c.K) return;
+        lo = next;
     }
 }
 
@@ -381,43 +460,41 @@ __device__ __forceinline__ uint32_t threshold(const Ctx &c, int i, const Level &
     __syncthreads();
     uint32_t T = all ? NONE : m0 + s_res[0], under = all ? 0u : s_res[1];
     if (nbins == HB && !all && s_res[0] == (uint32_t)(HB - 1)) {
-        // the K-th child is past the range: count the children 4096 values at
-        // a time (from the last bin's first value on) until it is found
-        constexpr int PER = HB / WT;
-        for (uint32_t lo = m0 + HB - 1;; lo += HB) {
-            __syncthreads();
-            for (int b = t; b < HB; b += WT) s_bin[b] = 0u;
-            __syncthreads();
-            for (uint32_t x = t; x < B * (uint32_t)(c.n2 + 1); x += WT) {
-                const uint32_t p = x % B;
-                const int u = (int)(x / B);
-                uint32_t d;
-                if (u == c.n2) {
-                    d = c.ped[i & 1][p] + (uint32_t)c.c.vdel + deg * (uint32_t)c.c.edel;
-                } else {
-                    if ((c.img[i & 1][(size_t)(u >> 5) * c.Kp + p] >> (u & 31)) & 1u) continue;
-                    d = child_ped(c, i, p, u, deg);
-                }
-                if (d >= lo && d - lo < (uint32_t)HB) atomicAdd(&s_bin[d - lo], 1u);
-            }
-            __syncthreads();
-            uint32_t mine = 0u, tot;
-            for (int q = 0; q < PER; ++q) mine += s_bin[t * PER + q];
-            const uint32_t below_me = under + block_excl_scan<NWV>(mine, s_tmp, &tot);
-            if (under + tot < K) {
-                under += tot;
-                continue;
-            }
-            find(below_me, mine, PER);
-            __syncthreads();
-            T = lo + s_res[0];
-            under = s_res[1];
-            break;
+        // the K-th child is past the range: its HB values, then its value
+        constexpr int PER = FC / WT, PERV = HB / WT;
+        uint32_t h[PER], mine = 0u, tot;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            h[q] = c.farc[t * PER + q];
+            mine += h[q];
         }
+        uint32_t at = under + block_excl_scan<NWV>(mine, s_tmp, &tot);
+        if (at < K && K <= at + mine) {
+#pragma unroll
+            for (int q = 0; q < PER; ++q) {
+                if (at < K && K <= at + h[q]) {
+                    s_res[0] = (uint32_t)(t * PER + q);
+                    s_res[1] = at;
+                }
+                at += h[q];
+            }
+        }
+        __syncthreads();
+        const uint32_t first_value = s_res[0] * (uint32_t)HB;
+        under = s_res[1];
+        for (int b = t; b < HB; b += WT) s_bin[b] = c.far[first_value + (uint32_t)b];
+        __syncthreads();
+        mine = 0u;
+        for (int q = 0; q < PERV; ++q) mine += s_bin[t * PERV + q];
+        find(under + block_excl_scan<NWV>(mine, s_tmp, &tot), mine, PERV);
+        __syncthreads();
+        T = m0 + first_value + s_res[0];
+        under = s_res[1];
     }
     if (blockIdx.x == 0 && t == 0) {
         Level *N = c.st + i + 1;
         c.st[i].quota = all ? 0u : K - under;
+        c.st[i].far = s_last == (uint32_t)(HB - 1) ? 1u : 0u;
         N->B = min(V, K);
         N->m0 = m0 + s_first;
         // (the last bin also holds what is above it)
@@ -461,7 +538,7 @@ __global__ __launch_bounds__(WT) void wm_mark(Ctx c, int i, int chunks, int grou
         // bytes: 0 below T, 1 at T, more above
         const float shift = (float)((int)(deg * (uint32_t)c.c.edel) - (int)T + 1);
         const int ls = wid * 16 + (lane & 15), q = lane >> 4;
-        tile.score(c, sl, s0, B, u0, shift, [&](int k, const v4f &y) {
+        tile.score(c, sl, t, s0, B, u0, shift, [&](int k, const v4f &y) {
             uint32_t w = 0u;
 #pragma unroll
             for (int r = 0; r < 4; ++r) w = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(y[r], 0.f, (float)XCAP), r, w);
@@ -603,6 +680,20 @@ __device__ __forceinline__ void prepare(const Ctx &c, int i) {
     if (t < MAXN / 32) c.prep->pc[t] = s_pc[t];
 }
 
+// The far histogram back to zero, after a level that used it: each
+// workgroup (but the last) its share of the groups that hold anything.
+template <int UT>
+__device__ __forceinline__ void clear_far(const Ctx &c) {
+    __shared__ uint32_t s_used[FC];
+    for (int x = threadIdx.x; x < FC; x += UT) s_used[x] = c.farc[x];
+    __syncthreads();
+    for (uint32_t g = blockIdx.x; g < (uint32_t)FC; g += gridDim.x - 1) {
+        if (s_used[g] == 0u) continue;   // (only its owner clears a sum)
+        for (int x = threadIdx.x; x < HB; x += UT) c.far[(size_t)g * HB + x] = 0u;
+        if (threadIdx.x == 0) c.farc[g] = 0u;
+    }
+}
+
 // The last workgroup prepares the next level; deg comes with the launch's own
 // reading of it, since Prep is being rewritten.
 // UT threads: 1024 while there are few groups, since the survivors gather
@@ -637,6 +728,7 @@ __global__ __launch_bounds__(UT) void wm_update(Ctx c, int i, int groups) {
     const uint32_t deg = sgpr(degree(c, i));
     const uint32_t B = sgpr(L.B), quota = sgpr(L.quota), Bn = sgpr(Bn0);
     const int b0 = (int)sgpr(L.b0);
+    if (sgpr(L.far)) clear_far<UT>(c);
     if (s0 >= B) return;
 #pragma unroll
     for (int k = 0; k < CWM; ++k) {
@@ -824,7 +916,7 @@ __global__ __launch_bounds__(WT) void wm_final_map(Ctx c, int groups) {
 // ------------------------------------------------------------------ host side
 
 struct Layout {
-    size_t ped[2], nsub[2], img[2], cur[2], anc[2], phi, com, sets, le, lt, cnt, rec, hist, st, prep, ce, best, total;
+    size_t ped[2], nsub[2], img[2], cur[2], anc[2], phi, com, sets, le, lt, cnt, rec, hist, far, farc, st, prep, ce, best, total;
 };
 
 uint32_t slot_stride(int K) { return (uint32_t)((K + GS - 1) / GS) * GS; }
@@ -853,6 +945,8 @@ Layout layout(int n1, int w2, uint32_t Kp) {
     L.cnt = take(2 * groups * 4);
     L.rec = take((size_t)Kp * 4);
     L.hist = take((size_t)HC * HB * 4);
+    L.far = take((size_t)FAR * 4);
+    L.farc = take((size_t)FC * 4);
     L.st = take((size_t)(n1 + 1) * sizeof(Level));
     L.prep = take(sizeof(Prep));
     L.ce = take(8);
@@ -863,7 +957,9 @@ Layout layout(int n1, int w2, uint32_t Kp) {
 
 template <int W>
 hipError_t levels(const Ctx &c, bool last_complete, hipStream_t stream) {
-    hipLaunchKernelGGL(wm_init, dim3(32), dim3(WT), 0, stream, c);
+    // (up to 16 MB to clear: 64 values a thread)
+    const uint32_t far = c.pedmax >= (uint32_t)(HB - 1) ? c.pedmax + 1u : 0u;
+    hipLaunchKernelGGL(wm_init, dim3(std::max(32u, far / (64 * WT))), dim3(WT), 0, stream, c);
     const int chunks = (c.n2 + 32 * CWD - 1) / (32 * CWD), groups = (int)(c.Kp / GS);
     uint64_t bound = 1;   // parents at level i are at most min(K, (n2 + 1)^i)
     for (int i = 0; i < c.n1; ++i) {
@@ -896,9 +992,9 @@ size_t widem_workspace_bytes(int n1, int w2, int K) { return layout(n1, w2, slot
 
 bool widem_takes(const GraphRec &g1, const GraphRec &g2, int planes, Costs c, uint64_t pedmax) {
     if (planes != 0 || g2.n <= kWide1MaxN2 || pedmax >= (uint64_t)kFastBound) return false;
-    // a level's range is the parents' spread (less than the largest increment
-    // of a level on the pairs measured) and that increment: three quarters of
-    // the bins leave it room; beyond, the selection would have to count by itself
+    // the largest increment of a level: while the bins hold it, the least child
+    // (the least parent's) lies among them, so a level's bins start at its least
+    // parent PED exactly.  Children past the bins go to the far histogram.
     const int64_t inc = (int64_t)c.vsub + (int64_t)c.vdel + (int64_t)std::max(c.edel, c.esub) * std::min(g1.n - 1, g1.m) +
                         (int64_t)c.eins * std::min(g1.n, g2.n);
     SlotCodes s;
@@ -911,7 +1007,8 @@ hipError_t launch_widem(const DbView &src, const DbView &dst, const GraphRec &g1
     const uint32_t Kp = slot_stride(K);
     const Layout L = layout(g1.n, g2.w, Kp);
     SlotCodes s;
-    if (K < 1 || K > kWideMaxK || L.total > ws_bytes || g1.n > MAXN || g2.n > MAXN || !slot_codes(costs, false, &s))
+    if (K < 1 || K > kWideMaxK || L.total > ws_bytes || g1.n > MAXN || g2.n > MAXN || pedmax >= FAR ||
+        !slot_codes(costs, false, &s))
         return hipErrorInvalidValue;
     char *base = static_cast<char *>(ws);
     Ctx c{};
@@ -946,6 +1043,8 @@ hipError_t launch_widem(const DbView &src, const DbView &dst, const GraphRec &g1
     c.cnt = reinterpret_cast<uint32_t *>(base + L.cnt);
     c.rec = reinterpret_cast<uint32_t *>(base + L.rec);
     c.hist = reinterpret_cast<uint32_t *>(base + L.hist);
+    c.far = reinterpret_cast<uint32_t *>(base + L.far);
+    c.farc = reinterpret_cast<uint32_t *>(base + L.farc);
     c.st = reinterpret_cast<Level *>(base + L.st);
     c.prep = reinterpret_cast<Prep *>(base + L.prep);
     c.ce = reinterpret_cast<unsigned long long *>(base + L.ce);
