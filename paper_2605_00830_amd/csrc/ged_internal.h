@@ -98,9 +98,9 @@ hipError_t launch_wide1(const DbView &src, const DbView &dst, const GraphRec &g1
                         int64_t *cand, int cus, hipStream_t stream);
 
 // ... and for larger targets without edge labels on the matrix cores
-// (kb_widem.hip), wherever widem_takes the costs.
+// (kb_widem.hip), wherever widem_takes the pair, its costs and K.
 size_t widem_workspace_bytes(int n1, int w2, int K);
-bool widem_takes(const GraphRec &g1, const GraphRec &g2, int planes, Costs c, uint64_t pedmax);
+bool widem_takes(const GraphRec &g1, const GraphRec &g2, int planes, Costs c, int K, uint64_t pedmax);
 hipError_t launch_widem(const DbView &src, const DbView &dst, const GraphRec &g1, const GraphRec &g2, Costs c, int K,
                         int last_complete, uint32_t pedmax, void *ws, size_t ws_bytes, int32_t *dist, int32_t *map,
                         int64_t *cand, hipStream_t stream);

@@ -944,7 +944,7 @@ hipError_t launch_wide(const DbView &src, const DbView &dst, const GraphRec &g1,
     if (g2.n <= kWide1MaxN2 && pedmax < (uint64_t)kWide1Bound)
         return launch_wide1(src, dst, g1, g2, costs, K, last_complete, (uint32_t)pedmax, ws, ws_bytes, dist, map, cand,
                             cus, stream);
-    if (widem_takes(g1, g2, planes, costs, pedmax))
+    if (widem_takes(g1, g2, planes, costs, K, pedmax))
         return launch_widem(src, dst, g1, g2, costs, K, last_complete, (uint32_t)pedmax, ws, ws_bytes, dist, map, cand,
                             stream);
     const int PL = planes == 0 ? 0 : (planes <= 2 ? 2 : 4);

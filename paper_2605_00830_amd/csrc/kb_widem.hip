@@ -990,8 +990,16 @@ hipError_t levels(const Ctx &c, bool last_complete, hipStream_t stream) {
 
 size_t widem_workspace_bytes(int n1, int w2, int K) { return layout(n1, w2, slot_stride(K)).total; }
 
-bool widem_takes(const GraphRec &g1, const GraphRec &g2, int planes, Costs c, uint64_t pedmax) {
+bool widem_takes(const GraphRec &g1, const GraphRec &g2, int planes, Costs c, int K, uint64_t pedmax) {
     if (planes != 0 || g2.n <= kWide1MaxN2 || pedmax >= (uint64_t)kFastBound) return false;
+    // the largest beams on small targets: here a level costs about 20 ns per 64
+    // slots whatever the target (workgroups of few children), while the candidate
+    // matrix's share goes with n2 and its mapping copies with n1.  Equal, measured,
+    // at K = 235,000 for 33 x 33 vertices (n1 x n2), 290,000 for 100 x 33, 520,000
+    // for 200 x 33, 330,000 for 48 x 48, 400,000 for 56 x 56; at two million slots
+    // 18.3 against 10.7 ms (33 x 33), 23.1 against 15.7 (40 x 40); from 64 target
+    // vertices on here is at most 4 % behind and up to twice as fast.
+    if (g2.n <= 60 && (int64_t)K * (7400 - 75 * g2.n - 14 * std::min(g1.n, 240)) > 1000000000) return false;
     // the largest increment of a level: while the bins hold it, the least child
     // (the least parent's) lies among them, so a level's bins start at its least
     // parent PED exactly.  Children past the bins go to the far histogram.
