@@ -99,12 +99,12 @@ struct Ctx {
     uint32_t *cnt;           // [2][groups] below T, equal to T per 64 slots
     uint32_t *rec;           // [Kp]
     uint32_t *hist;          // [HC][HB]
-    uint32_t *far, *farc;    // [FAR] children past the histogram, by value above the least parent PED; [FC] sums
     Level *st;
     Prep *prep;
     unsigned long long *ce, *best;   // best: a key per workgroup
     int32_t *out_dist, *out_map;
     int64_t *out_cand;
+    uint32_t *far, *farc;    // [FAR] children past the histogram, by value above the least parent PED; [FC] sums
 };
 
 __device__ __forceinline__ uint32_t sgpr(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
@@ -916,7 +916,7 @@ __global__ __launch_bounds__(WT) void wm_final_map(Ctx c, int groups) {
 // ------------------------------------------------------------------ host side
 
 struct Layout {
-    size_t ped[2], nsub[2], img[2], cur[2], anc[2], phi, com, sets, le, lt, cnt, rec, hist, far, farc, st, prep, ce, best, total;
+    size_t ped[2], nsub[2], img[2], cur[2], anc[2], phi, com, sets, le, lt, cnt, rec, hist, st, prep, ce, best, far, farc, total;
 };
 
 uint32_t slot_stride(int K) { return (uint32_t)((K + GS - 1) / GS) * GS; }
@@ -945,12 +945,14 @@ Layout layout(int n1, int w2, uint32_t Kp) {
     L.cnt = take(2 * groups * 4);
     L.rec = take((size_t)Kp * 4);
     L.hist = take((size_t)HC * HB * 4);
-    L.far = take((size_t)FAR * 4);
-    L.farc = take((size_t)FC * 4);
     L.st = take((size_t)(n1 + 1) * sizeof(Level));
     L.prep = take(sizeof(Prep));
     L.ce = take(8);
     L.best = take(groups * 8);
+    // (last: few levels touch them, and between the others they would put what
+    // every level touches on further pages, 0.4 us of each of its launches)
+    L.farc = take((size_t)FC * 4);
+    L.far = take((size_t)FAR * 4);
     L.total = off;
     return L;
 }
