@@ -26,16 +26,27 @@ struct BlockShape {
     int BT;      // threads per workgroup: kBlockThreads or kBlockThreadsWide
     int directed = 0;   // directed database: W covers an out-row and an in-row
     int K = 0;          // beam width
+    bool mat_only = false;   // the matrix-core kernel wherever it has an instantiation (less workspace)
 };
 
 // Slot stride of the workgroup kernel for beam width K and `threads` per
 // workgroup (64, 128, 256, or K rounded up to a multiple of `threads`):
 // BlockShape::KS must equal it.
 int block_slot_stride(int K, int threads);
+// Per workgroup, and the most workgroups a CU holds, of any kernel that
+// launch_block may choose for the shape (by the costs and the number of pairs).
 size_t block_workspace_bytes(const BlockShape &s);
-// An instantiation exists for this shape (every shape at 256 and 512 threads).
-bool block_shape_supported(const BlockShape &s);
 hipError_t block_max_resident(const BlockShape &s, int *blocks_per_cu);
+// ... of each of the two (0: never chosen for the shape).
+hipError_t block_residents(const BlockShape &s, int *mat, int *cand);
+// This number of threads is a configuration of its own for the shape (256 and
+// 512 always).
+bool block_shape_supported(const BlockShape &s);
+// What launch_block would launch: whether it is the matrix-core kernel (a caller
+// that knows the costs before it sizes the workspace sets mat_only then), and
+// the kernel itself.
+bool block_takes_mat(const BlockShape &s, const Costs &c, int64_t nwork, int cus);
+const void *block_kernel(const BlockShape &s, const Costs &c, int nwork, int cus);
 // last_complete: at the last level every child is completed (Sec. 4.4.1) and
 // only the least total is kept, instead of the K of least partial distance
 // (the same argument of every launch below).
@@ -43,8 +54,12 @@ hipError_t launch_block(const BlockShape &s, const DbView &src, const DbView &ds
                         int *queue, Costs c, int K, int last_complete, void *workspace, size_t ws_stride,
                         Outputs out, int grid, hipStream_t stream);
 // The matrix-core form of the workgroup kernel (kb_mat.h), which the block_*
-// functions use wherever it has an instantiation for the shape.
+// functions use wherever it has an instantiation for the shape, but for the
+// small targets that cand_faster (kb_block.hip) leaves to the other.
 bool mat_supported(const BlockShape &s);
+// The costs ride in the matrix operands (kb_mat.h: FAST).
+bool mat_fast(const BlockShape &s, const Costs &c);
+const void *mat_kernel_for(const BlockShape &s, const Costs &c);
 size_t mat_workspace_bytes(const BlockShape &s);
 hipError_t mat_max_resident(const BlockShape &s, int *blocks_per_cu);
 hipError_t launch_mat(const BlockShape &s, const DbView &src, const DbView &dst, const WorkItem *work, int nwork,

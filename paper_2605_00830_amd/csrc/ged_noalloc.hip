@@ -110,6 +110,7 @@ extern "C" ged_status ged_kbest_noalloc(ged_db *db, const ged_pair *h_pairs, int
     st = scratch_on(dev, &base);
     if (st != GED_OK) return st;
 
+    const gedk::Costs c{costs.vsub, costs.vdel, costs.vins, costs.esub, costs.edel, costs.eins};
     // ---- the scratch's layout: staging, then one workspace share per
     // workgroup-kernel bin
     const int PL = db->planes == 0 ? 0 : (db->planes <= 2 ? 2 : 4);
@@ -133,8 +134,18 @@ extern "C" ged_status ged_kbest_noalloc(ged_db *db, const ged_pair *h_pairs, int
         const int threads = count[b] < 2 * (int64_t)cus ? gedk::kBlockThreadsWide : gedk::kBlockThreads;
         shape[b] = gedk::BlockShape{gedk::bin_words(b), PL, gedk::block_slot_stride(K, threads), nmax1[b], nmax2[b],
                                     threads, directed, K};
+        shape[b].mat_only = gedk::block_takes_mat(shape[b], c, count[b], cus);
         stride[b] = gedk::block_workspace_bytes(shape[b]);
         reserve += (stride[b] + 255) & ~(size_t)255;
+    }
+    if (cv.off + reserve > kScratchBytes) {   // the kernel of less workspace
+        reserve = 0;
+        for (int b = gedk::kWaveFamilies; b < gedk::kPairBins; ++b) {
+            if (count[b] == 0) continue;
+            shape[b].mat_only = true;
+            stride[b] = gedk::block_workspace_bytes(shape[b]);
+            reserve += (stride[b] + 255) & ~(size_t)255;
+        }
     }
     if (cv.off + reserve > kScratchBytes)
         return fail(GED_EUNSUPPORTED, "the batch needs %zu bytes of staging, more than the %zu-byte scratch",
@@ -172,7 +183,6 @@ extern "C" ged_status ged_kbest_noalloc(ged_db *db, const ged_pair *h_pairs, int
     GED_HIP(gedk::launch_map_offsets(db->d_graphs, db->count, pairs, npairs, moff, s));
     GED_HIP(gedk::launch_classify_pairs(db->d_graphs, pairs, npairs, moff, K, directed, lists, lb, cnt, s));
     const gedk::DbView view{db->d_graphs, db->d_adj, db->d_vlab, db->planes};
-    const gedk::Costs c{costs.vsub, costs.vdel, costs.vins, costs.esub, costs.edel, costs.eins};
     const gedk::Outputs out{d_dist, d_map, nullptr};
     int *queue = cnt + gedk::kPairBins;
     for (int b = 0; b < gedk::kPairBins; ++b) {

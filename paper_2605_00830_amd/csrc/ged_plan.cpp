@@ -41,7 +41,9 @@ struct Bin {
     gedk::BlockShape shape{};    // workgroup-kernel instantiation and workspace shape
     std::vector<WorkItem> h_sorted;   // longest first
     std::vector<WorkItem> h_work;     // launch order for the current grid (deal_alternating)
-    WorkItem *d_work = nullptr;  // in the plan's slab, as the next
+    bool both = false;           // a run's costs choose between the two workgroup kernels:
+    std::vector<WorkItem> h_cand;     // ... h_work is for the matrix-core one's grid, this for the other's
+    WorkItem *d_work = nullptr, *d_cand = nullptr;   // in the plan's slab, as the next
     int *d_queue = nullptr;      // [1 + nwork]: batched counter, then one per pair
     void *d_ws = nullptr;        // workgroup-kernel workspace
     size_t ws_stride = 0;
@@ -49,7 +51,10 @@ struct Bin {
     int grid = 0;                // current persistent grid
     int groups_per_cu = 0;       // current resident workgroups per CU
     int max_wave_per_cu = 0;     // occupancy limits
-    int max_block_per_cu[3] = {0, 0, 0};   // workgroups of 256, 512, 1024 threads (0: no such instantiation)
+    // workgroups of 256, 512, 1024 threads of either kernel (0: not a configuration
+    // of its own), and of the matrix-core and the candidate-matrix kernel apart
+    int max_block_per_cu[3] = {0, 0, 0};
+    int mat_per_cu[3] = {0, 0, 0}, cand_per_cu[3] = {0, 0, 0};
 };
 
 int bt_index(int threads) {
@@ -211,7 +216,16 @@ ged_status configure_bin(ged_plan *p, Bin &b, bool wave, int groups_per_cu, int 
         }
     }
     b.h_work = b.h_sorted;
-    gedh::deal_alternating(b.h_work, grid, wave ? 4 * (int64_t)p->cus : (int64_t)p->cus);
+    if (!wave && b.both) {
+        const int k = bt_index(threads);
+        b.h_cand = b.h_sorted;
+        gedh::deal_alternating(b.h_work, std::min<int64_t>(grid, (int64_t)b.mat_per_cu[k] * p->cus), p->cus);
+        gedh::deal_alternating(b.h_cand, std::min<int64_t>(grid, (int64_t)b.cand_per_cu[k] * p->cus), p->cus);
+        if (upload)
+            GED_HIP(hipMemcpy(b.d_cand, b.h_cand.data(), sizeof(WorkItem) * (size_t)nwork, hipMemcpyHostToDevice));
+    } else {
+        gedh::deal_alternating(b.h_work, grid, wave ? 4 * (int64_t)p->cus : (int64_t)p->cus);
+    }
     if (upload)
         GED_HIP(hipMemcpy(b.d_work, b.h_work.data(), sizeof(WorkItem) * (size_t)nwork, hipMemcpyHostToDevice));
     b.wave = wave;
@@ -250,7 +264,8 @@ ged_status launch_bin(const ged_plan *p, const Bin &b, const RunCtx &r, bool per
                                                  b.shape.directed));
         }
     } else if (!perpair) {
-        GED_HIP(gedk::launch_block(b.shape, r.view, r.view, b.d_work, nwork, b.d_queue, r.c, p->K, p->last_complete,
+        const bool cand = b.both && !gedk::block_takes_mat(b.shape, r.c, nwork, p->cus);
+        GED_HIP(gedk::launch_block(b.shape, r.view, r.view, cand ? b.d_cand : b.d_work, nwork, b.d_queue, r.c, p->K, p->last_complete,
                                    b.d_ws, b.ws_stride, r.o, b.grid, r.s));
     } else {
         for (int i = 0; i < nwork; ++i)
@@ -577,7 +592,9 @@ ged_status ged_plan_create_ex(ged_db *db, const ged_pair *h_pairs, int64_t npair
             sh.BT = bt_of(k);
             sh.KS = gedk::block_slot_stride(K, sh.BT);
             if (k == 2 && !gedk::block_shape_supported(sh)) continue;   // 1024 threads: some shapes only
-            e = gedk::block_max_resident(sh, &b.max_block_per_cu[k]);
+            e = gedk::block_residents(sh, &b.mat_per_cu[k], &b.cand_per_cu[k]);
+            b.max_block_per_cu[k] = std::max(b.mat_per_cu[k], b.cand_per_cu[k]);
+            b.both = b.both || (b.mat_per_cu[k] > 0 && b.cand_per_cu[k] > 0);
         }
         if (e == hipSuccess && b.wave_ok)
             e = gedk::wave_family_max_resident(b.wave_words, b.shape.PL, K, p->last_complete, &b.max_wave_per_cu,
@@ -607,16 +624,20 @@ ged_status ged_plan_create_ex(ged_db *db, const ged_pair *h_pairs, int64_t npair
     };
     const size_t o_status = take(sizeof(int32_t) * (size_t)std::max<int64_t>(npairs, 1));
     const size_t o_aside = take(sizeof(WorkItem) * h_aside.size());
-    std::vector<size_t> o_queue, o_work;
+    std::vector<size_t> o_queue, o_work, o_cand;
     for (const Bin &b : p->bins) {
         o_queue.push_back(take(sizeof(int) * (b.h_work.size() + 1)));
         o_work.push_back(take(sizeof(WorkItem) * b.h_work.size()));
+        o_cand.push_back(take(b.both ? sizeof(WorkItem) * b.h_work.size() : 0));
     }
     std::vector<char> image(bytes, 0);
     if (npairs > 0) memcpy(image.data() + o_status, h_status.data(), sizeof(int32_t) * (size_t)npairs);
     if (p->naside > 0) memcpy(image.data() + o_aside, h_aside.data(), sizeof(WorkItem) * h_aside.size());
-    for (size_t k = 0; k < p->bins.size(); ++k)
-        memcpy(image.data() + o_work[k], p->bins[k].h_work.data(), sizeof(WorkItem) * p->bins[k].h_work.size());
+    for (size_t k = 0; k < p->bins.size(); ++k) {
+        const Bin &b = p->bins[k];
+        memcpy(image.data() + o_work[k], b.h_work.data(), sizeof(WorkItem) * b.h_work.size());
+        if (!b.h_cand.empty()) memcpy(image.data() + o_cand[k], b.h_cand.data(), sizeof(WorkItem) * b.h_cand.size());
+    }
     e = hipMalloc(&p->d_slab, bytes);
     if (e == hipSuccess) e = hipMemcpy(p->d_slab, image.data(), bytes, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
@@ -629,6 +650,7 @@ ged_status ged_plan_create_ex(ged_db *db, const ged_pair *h_pairs, int64_t npair
     for (size_t k = 0; k < p->bins.size(); ++k) {
         p->bins[k].d_queue = reinterpret_cast<int *>(slab + o_queue[k]);
         p->bins[k].d_work = reinterpret_cast<WorkItem *>(slab + o_work[k]);
+        p->bins[k].d_cand = reinterpret_cast<WorkItem *>(slab + o_cand[k]);
     }
     *out = p;
     return ok();

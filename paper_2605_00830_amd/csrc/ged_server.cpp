@@ -331,7 +331,12 @@ hipError_t launch_batch(ged_server *s, Slab &b) {
             const int wide = cnt < 2 * s->cus ? 1 : 0;
             shape[bin] = shape_for(s, 1 << (bin - kWaveBins), nmax1[bin], nmax2[bin],
                                    wide ? gedk::kBlockThreadsWide : gedk::kBlockThreads);
+            shape[bin].mat_only = gedk::block_takes_mat(shape[bin], s->c, cnt, s->cus);
             stride[bin] = gedk::block_workspace_bytes(shape[bin]);
+            if (stride[bin] > b.ws_bytes) {   // (a workspace holds one workgroup of every shape so)
+                shape[bin].mat_only = true;
+                stride[bin] = gedk::block_workspace_bytes(shape[bin]);
+            }
             const int fit = (int)std::min<size_t>(b.ws_bytes / stride[bin], (size_t)std::numeric_limits<int>::max());
             // the workgroup classes hold at most kBlockClassPerCu[class]
             // workgroups per CU: a batch of large queries at full occupancy
@@ -572,9 +577,10 @@ ged_status ged_server_create(ged_db *db, const ged_server_config *config, ged_se
             const int W = 1 << k;
             if (W > (s->directed ? 2 : 1) && per_word * W / 2 >= max_n[cls]) break;   // W / 2 words already cover it
             for (int wide = 0; wide < 2 && e == hipSuccess; ++wide) {
-                const gedk::BlockShape sh = shape_for(s, W, max_n[cls], std::min(per_word * W, max_n[cls]),
-                                                      wide ? gedk::kBlockThreadsWide : gedk::kBlockThreads);
+                gedk::BlockShape sh = shape_for(s, W, max_n[cls], std::min(per_word * W, max_n[cls]),
+                                                wide ? gedk::kBlockThreadsWide : gedk::kBlockThreads);
                 e = gedk::block_max_resident(sh, &s->block_per_cu[wide][k]);
+                sh.mat_only = true;   // what the least workspace has to hold
                 const int64_t grid =
                     std::min<int64_t>((int64_t)cfg.max_batch, (int64_t)s->block_per_cu[wide][k] * s->cus);
                 one_block = std::max(one_block, gedk::block_workspace_bytes(sh));

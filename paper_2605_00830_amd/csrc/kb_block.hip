@@ -1,7 +1,8 @@
 // kb_block.hip -- workgroup-per-pair K-Best search for gfx950 (any shape up
 // to 512 vertices and K = 1024): the block_* entry points, and the kernel for
 // the shapes without a matrix-core instantiation (kb_mat.h: more than four
-// edge-label codes, the largest K, state beyond its LDS).
+// edge-label codes, the largest K, state beyond its LDS) and the small targets
+// that are faster without it (cand_faster).
 //
 // One 256-thread workgroup searches one pair at a time: first the pair at
 // its own index, then further pairs from a work queue (persistent launch).
@@ -52,6 +53,9 @@
 // sets its Phi bit in the upper half.  The same popcounts then count kept,
 // deleted, inserted and relabelled arcs of both directions at once: the
 // implied operations of Sec. 2.3 taken for each arc direction.
+#include <algorithm>
+#include <limits>
+
 #include "ged_internal.h"
 
 namespace gedk {
@@ -820,16 +824,15 @@ const void *select_kernel(int W, int PL, bool CL, int BT, bool DIR) {
 #define GEDK_CASE(w, pl, cl, bt, d) \
     if (W == w && PL == pl && CL == cl && BT == bt && DIR == d) return kernel_ptr<w, pl, cl, bt, d>();
 #define GEDK_ROW(w, cl, bt, d) GEDK_CASE(w, 0, cl, bt, d) GEDK_CASE(w, 2, cl, bt, d) GEDK_CASE(w, 4, cl, bt, d)
-    // (candidate matrix in LDS: without the shapes that only the matrix-core
-    // kernel's range of K could fit there)
+    // the shapes without a matrix-core instantiation and those of cand_faster
+    // (of any K and sizes; walked over all of them on the host)
 #define GEDK_ALL(bt)                                                                                        \
     GEDK_ROW(1, true, bt, false) GEDK_ROW(2, true, bt, false) GEDK_CASE(4, 4, true, bt, false)               \
-    GEDK_CASE(8, 4, true, bt, false) GEDK_CASE(16, 2, true, bt, false) GEDK_CASE(16, 4, true, bt, false)     \
-    GEDK_ROW(1, false, bt, false) GEDK_ROW(2, false, bt, false) GEDK_ROW(4, false, bt, false)                \
-    GEDK_ROW(8, false, bt, false) GEDK_ROW(16, false, bt, false) GEDK_ROW(2, true, bt, true)                 \
-    GEDK_ROW(4, true, bt, true) GEDK_CASE(8, 4, true, bt, true) GEDK_CASE(16, 2, true, bt, true)             \
-    GEDK_CASE(16, 4, true, bt, true) GEDK_ROW(2, false, bt, true) GEDK_ROW(4, false, bt, true)               \
-    GEDK_ROW(8, false, bt, true) GEDK_ROW(16, false, bt, true)
+    GEDK_CASE(8, 4, true, bt, false) GEDK_CASE(16, 4, true, bt, false) GEDK_ROW(2, false, bt, false)         \
+    GEDK_ROW(4, false, bt, false) GEDK_ROW(8, false, bt, false) GEDK_ROW(16, false, bt, false)               \
+    GEDK_ROW(2, true, bt, true) GEDK_ROW(4, true, bt, true) GEDK_CASE(8, 4, true, bt, true)                  \
+    GEDK_CASE(16, 4, true, bt, true) GEDK_ROW(4, false, bt, true) GEDK_ROW(8, false, bt, true)               \
+    GEDK_ROW(16, false, bt, true)
     GEDK_ALL(256)
     GEDK_ALL(512)
     // four waves per SIMD on one pair: the largest rows without label planes
@@ -849,28 +852,116 @@ int block_slot_stride(int K, int threads) {
     return (K + threads - 1) / threads * threads;
 }
 
+namespace {
+
+// Where both kernels serve a shape: whether the candidate matrix is the faster.
+// The matrix-core kernel pads targets to 128 vertices (four words), and costs
+// outside its operands (`fast` false) double its contractions and its
+// registers, so small targets are better off without it: this kernel then
+// holds several pairs per CU.  Measured (time with the candidate matrix over
+// time without: below 1 it is the faster), at 10..30 target vertices of 50, 300
+// and 1500 pairs unless said; `many`: 256-thread workgroups, as bins of at least
+// two pairs per CU have them.
+//   fast      one word, many, K 65..256 0.5..0.85, to 512 0.8..0.99 (directed 1.0..1.1), past it 1.3..1.7; few pairs
+//             1.1..1.5; sources past 128 vertices 1.2 and more.  Directed with labels past K = 512: 0.8..0.98 (many:
+//             0.89 to K = 768, 1.17 at 1024); two words, many 0.88 to K = 768, 1.22 at 1024
+//   not fast  one word, many, K 17..64 0.7..0.93, past it 0.33..0.9 (directed 0.9..1.26 to K = 32; unlabelled 1.14 at
+//             1024); few pairs, K past 128 0.5..1.0 (directed 1.05..1.2 to K = 256, past it 0.7..1.0)
+//             one and two words, sources past 128 vertices, K 65..128, more pairs than CUs 0.68..0.98 and 0.87..1.04
+//             (up to 300 and 200 source vertices; longer ones 1.0..1.4; at most a pair per CU 1.3..1.6)
+//             two words, K past 512: many 0.57..0.85 (directed 0.81 and 0.91, 1.22 at 1024), few 0.91..0.96 up to 640;
+//             with labels K 257..512, few 0.75..0.84 (many 1.2); directed with labels past 512 0.4..0.75
+//             four words directed (65..128 vertices) with labels, K 257..512, few 0.88..0.99 (many 1.1)
+// everywhere else the matrix cores are up to 19 times as fast.
+bool cand_faster(const BlockShape &s, bool fast, int64_t nwork, int cus) {
+    const int K = s.K, wt = s.directed ? s.W / 2 : s.W;   // words of a target
+    const bool many = s.BT == kBlockThreads, lab = s.PL > 0, dir = s.directed != 0, shortsrc = s.nmax1 <= 128;
+    if (fast) {
+        if (dir && lab && K > 512) return many ? wt <= 2 && K <= 896 : wt == 1;
+        return wt == 1 && many && shortsrc && K > 64 && K <= (dir ? 256 : 512);
+    }
+    const bool narrow = K > 64 && K <= 128;
+    if (wt == 1) {
+        if (!shortsrc) return (narrow && nwork > cus && s.nmax1 <= 300) || (lab && !dir && !many && K > 256);
+        return many ? K > (dir ? 32 : 16) && !(dir && !lab && K > 896) : K > (dir ? 256 : 128);
+    }
+    if (wt == 2) {
+        if (K > 512) return (dir && lab) || (many ? !dir || K <= 896 : !dir && K <= 640);
+        if (K > 256) return lab && !dir && !many;
+        return narrow && (shortsrc ? many : nwork > cus && s.nmax1 <= 200);
+    }
+    return wt == 4 && dir && lab && !many && K > 256;
+}
+
+// ... for some costs and some number of pairs (cand_faster grows with it).
+bool cand_possible(const BlockShape &s) {
+    const int64_t pairs = std::numeric_limits<int64_t>::max();
+    return !mat_supported(s) || (!s.mat_only && (cand_faster(s, true, pairs, 1) || cand_faster(s, false, pairs, 1)));
+}
+
+const void *cand_kernel(const BlockShape &s) {
+    return select_kernel(s.W, s.PL, cand_in_lds(s), s.BT, s.directed != 0);
+}
+
+hipError_t cand_max_resident(const BlockShape &s, int *blocks_per_cu) {
+    const void *k = cand_kernel(s);
+    if (!k) return hipErrorInvalidValue;
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k, s.BT, dyn_lds_bytes(s));
+}
+
+}  // namespace
+
 size_t block_workspace_bytes(const BlockShape &s) {
-    return mat_supported(s) ? mat_workspace_bytes(s) : layout_for(s).stride;
+    return std::max(mat_supported(s) ? mat_workspace_bytes(s) : 0, cand_possible(s) ? layout_for(s).stride : 0);
 }
 
 bool block_shape_supported(const BlockShape &s) {
-    return mat_supported(s) || select_kernel(s.W, s.PL, cand_in_lds(s), s.BT, s.directed != 0) != nullptr;
+    if (mat_supported(s) && s.BT > kBlockThreadsWide) return false;   // (the same kernel as at 512 threads)
+    return (mat_supported(s) && !cand_possible(s)) || cand_kernel(s) != nullptr;
+}
+
+hipError_t block_residents(const BlockShape &s, int *mat, int *cand) {
+    *mat = *cand = 0;
+    hipError_t e = mat_supported(s) ? mat_max_resident(s, mat) : hipSuccess;
+    if (e == hipSuccess && cand_possible(s)) e = cand_max_resident(s, cand);
+    return e;
 }
 
 hipError_t block_max_resident(const BlockShape &s, int *blocks_per_cu) {
-    if (mat_supported(s)) return mat_max_resident(s, blocks_per_cu);
-    const void *k = select_kernel(s.W, s.PL, cand_in_lds(s), s.BT, s.directed != 0);
-    if (!k) return hipErrorInvalidValue;
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k, s.BT, dyn_lds_bytes(s));
+    int mat = 0, cand = 0;
+    const hipError_t e = block_residents(s, &mat, &cand);
+    *blocks_per_cu = std::max(mat, cand);
+    return e;
+}
+
+bool block_takes_mat(const BlockShape &s, const Costs &c, int64_t nwork, int cus) {
+    return mat_supported(s) && (s.mat_only || !cand_faster(s, mat_fast(s, c), nwork, cus));
+}
+
+const void *block_kernel(const BlockShape &s, const Costs &c, int nwork, int cus) {
+    return block_takes_mat(s, c, nwork, cus) ? mat_kernel_for(s, c) : cand_kernel(s);
 }
 
 hipError_t launch_block(const BlockShape &s, const DbView &src, const DbView &dst, const WorkItem *work, int nwork,
                         int *queue, Costs c, int K, int last_complete, void *workspace, size_t ws_stride,
                         Outputs out, int grid, hipStream_t stream) {
     if (K != s.K) return hipErrorInvalidValue;
-    if (mat_supported(s))
+    bool mat = mat_supported(s);
+    if (mat && cand_possible(s)) {
+        // the grid is as large as the roomier of the two kernels': a persistent
+        // launch holds no more workgroups than are resident at once
+        int dev = 0, cus = 0, per_cu = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e != hipSuccess) return e;
+        mat = block_takes_mat(s, c, nwork, cus);
+        e = mat ? mat_max_resident(s, &per_cu) : cand_max_resident(s, &per_cu);
+        if (e != hipSuccess) return e;
+        grid = std::min(grid, per_cu * cus);
+    }
+    if (mat)
         return launch_mat(s, src, dst, work, nwork, queue, c, last_complete, workspace, ws_stride, out, grid, stream);
-    const void *k = select_kernel(s.W, s.PL, cand_in_lds(s), s.BT, s.directed != 0);
+    const void *k = cand_kernel(s);
     if (!k || grid <= 0 || s.KS != block_slot_stride(K, s.BT)) return hipErrorInvalidValue;
     BlockArgs a;
     a.src = src;
@@ -887,7 +978,7 @@ hipError_t launch_block(const BlockShape &s, const DbView &src, const DbView &ds
     a.planes_lds = planes_in_lds(s) ? 1 : 0;
     a.ws = static_cast<char *>(workspace);
     a.L = layout_for(s);
-    if (a.L.stride != ws_stride) return hipErrorInvalidValue;
+    if (a.L.stride > ws_stride) return hipErrorInvalidValue;   // (it may be more)
     a.out = out;
     void *args[] = {&a};
     return hipLaunchKernel(k, dim3(grid), dim3(s.BT), args, dyn_lds_bytes(s), stream);

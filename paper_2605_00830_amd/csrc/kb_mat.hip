@@ -85,11 +85,29 @@ hipError_t mat_max_resident(const BlockShape &s, int *blocks_per_cu) {
                                                         lds_bytes(s, m));
 }
 
+namespace {
+
+// The largest PED of any pair of the shape's orders.
+int64_t ped_bound(const BlockShape &s, const Costs &c) {
+    const int64_t vmax = std::max({c.vsub, c.vdel, c.vins}), emax = std::max({c.esub, c.edel, c.eins});
+    const int64_t e1 = (int64_t)s.nmax1 * (s.nmax1 - 1), e2 = (int64_t)s.nmax2 * (s.nmax2 - 1);
+    return vmax * ((int64_t)s.nmax1 + s.nmax2) + emax * (s.directed ? e1 + e2 : (e1 + e2) / 2);
+}
+
+}  // namespace
+
+bool mat_fast(const BlockShape &s, const Costs &c) {
+    SlotCodes codes;
+    return ped_bound(s, c) < kFastBound && slot_codes(c, s.PL > 0, &codes);
+}
+
+const void *mat_kernel_for(const BlockShape &s, const Costs &c) { return mat_kernel(s, mat_config(s), mat_fast(s, c)); }
+
 hipError_t launch_mat(const BlockShape &s, const DbView &src, const DbView &dst, const WorkItem *work, int nwork,
                       int *queue, Costs c, int last_complete, void *workspace, size_t ws_stride, Outputs out,
                       int grid, hipStream_t stream) {
     const MatConfig m = mat_config(s);
-    if (m.W == 0 || grid <= 0 || ws_stride != mat_workspace_bytes(s)) return hipErrorInvalidValue;
+    if (m.W == 0 || grid <= 0 || ws_stride < mat_workspace_bytes(s)) return hipErrorInvalidValue;
     MatArgs a{};
     a.src = src;
     a.dst = dst;
@@ -100,21 +118,16 @@ hipError_t launch_mat(const BlockShape &s, const DbView &src, const DbView &dst,
     a.K = s.K;
     a.last_complete = last_complete;
     a.ws = static_cast<char *>(workspace);
-    a.ws_stride = ws_stride;
+    a.ws_stride = mat_workspace_bytes(s);   // (what the caller has a workgroup may be more)
     a.out = out;
-    // the largest PED of any pair of these orders, and whether the costs fit
-    // the matrix operands
-    const int64_t vmax = std::max({c.vsub, c.vdel, c.vins}), emax = std::max({c.esub, c.edel, c.eins});
-    const int64_t e1 = (int64_t)s.nmax1 * (s.nmax1 - 1), e2 = (int64_t)s.nmax2 * (s.nmax2 - 1);
-    const int64_t bound = vmax * ((int64_t)s.nmax1 + s.nmax2) + emax * (s.directed ? e1 + e2 : (e1 + e2) / 2);
-    a.pedbound = (uint32_t)std::min<int64_t>(bound, 0x7fffffff);
+    a.pedbound = (uint32_t)std::min<int64_t>(ped_bound(s, c), 0x7fffffff);
     SlotCodes codes;
-    const bool fast = bound < kFastBound && slot_codes(c, s.PL > 0, &codes);
+    slot_codes(c, s.PL > 0, &codes);   // (used where mat_fast holds)
     a.code_img = codes.img;
     a.code_phi = codes.phi;
     a.code_same = codes.same;
     a.unit_exp = codes.unit_exp;
-    const void *k = mat_kernel(s, m, fast);
+    const void *k = mat_kernel_for(s, c);
     if (!k) return hipErrorInvalidValue;
     void *args[] = {&a};
     return hipLaunchKernel(k, dim3(grid), dim3(64 * m.SW * m.UW), args, (size_t)lds_bytes(s, m), stream);
