@@ -1197,8 +1197,12 @@ const void *mat_select(const MatConfig &m) {
     if (m.W == w && m.NT == nt && m.SW == sw && m.UW == uw)     \
         return reinterpret_cast<const void *>(&kb_mat_kernel<w, nt, sw, uw, LAB, DIR, FAST>);
 #define GEDK_MW(nt, sw, uw) GEDK_M(4, nt, sw, uw) GEDK_M(8, nt, sw, uw) GEDK_M(16, nt, sw, uw)
-    GEDK_MW(1, 1, 4) GEDK_MW(1, 2, 2) GEDK_MW(1, 4, 1) GEDK_MW(1, 4, 2) GEDK_MW(1, 8, 1) GEDK_MW(2, 8, 1)
-    GEDK_M(4, 4, 8, 1) GEDK_M(8, 4, 8, 1) GEDK_M(4, 4, 16, 1)
+    GEDK_MW(1, 1, 4) GEDK_MW(1, 2, 2) GEDK_MW(1, 4, 1) GEDK_MW(1, 4, 2)
+    GEDK_M(4, 1, 8, 1) GEDK_M(8, 1, 8, 1) GEDK_M(4, 2, 8, 1) GEDK_M(8, 2, 8, 1) GEDK_M(4, 4, 8, 1)
+    // the largest states: LDS holds them without label planes, some with those of
+    // directed graphs, whose rows are half as many
+    if constexpr (!LAB) { GEDK_M(16, 2, 8, 1) }
+    if constexpr (!LAB || DIR) { GEDK_M(16, 1, 8, 1) GEDK_M(8, 4, 8, 1) GEDK_M(4, 4, 16, 1) }
 #undef GEDK_MW
 #undef GEDK_M
     return nullptr;
