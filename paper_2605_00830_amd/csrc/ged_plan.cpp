@@ -359,13 +359,27 @@ std::string device_key() {
     return buf;
 }
 
-std::string bin_key(const std::string &dev, int K, int last_complete, const Bin &b) {
+// The workgroup bin's shape at 256, 512 or 1024 threads.
+gedk::BlockShape shape_at(const Bin &b, int K, int threads) {
+    gedk::BlockShape s = b.shape;
+    s.BT = threads;
+    s.KS = gedk::block_slot_stride(K, threads);
+    return s;
+}
+
+// (ends with which workgroup kernel these costs take at 256 and at 512 threads,
+// m = matrix cores, c = candidate matrix: a line measured on another kernel
+// does not hold)
+std::string bin_key(const std::string &dev, int K, int last_complete, const Bin &b, const gedk::Costs &c, int cus) {
     int lg = 0;
+    char kind[4] = "";
+    for (int k = 0; k < 2 && !b.bip; ++k)
+        kind[k] = gedk::block_takes_mat(shape_at(b, K, bt_of(k)), c, (int64_t)b.h_sorted.size(), cus) ? 'm' : 'c';
     while ((1ll << (lg + 1)) <= (long long)b.h_work.size()) ++lg;
     char buf[256];
-    snprintf(buf, sizeof buf, "%s|K%d%s%s%s|w%d|W%d|PL%d|n%d|m%d|p2^%d", dev.c_str(), K, last_complete ? "c" : "",
+    snprintf(buf, sizeof buf, "%s|K%d%s%s%s|w%d|W%d|PL%d|n%d|m%d|p2^%d%s%s", dev.c_str(), K, last_complete ? "c" : "",
              b.bip ? "bip" : "", b.shape.directed ? "dir" : "", b.bip ? b.bip_cpl : (b.wave_ok ? b.wave_words : 0), b.shape.W, b.shape.PL,
-             b.shape.nmax1, b.shape.nmax2, lg);
+             b.shape.nmax1, b.shape.nmax2, lg, b.bip ? "" : "|", kind);
     return buf;
 }
 
@@ -775,7 +789,7 @@ ged_status ged_plan_tune(ged_plan *plan, ged_costs costs, int32_t *d_dist, int32
     GED_HIP(hipEventCreate(&e0));
     GED_HIP(hipEventCreate(&e1));
     for (Bin &b : plan->bins) {
-        const std::string key = bin_key(dev, plan->K, plan->last_complete, b);
+        const std::string key = bin_key(dev, plan->K, plan->last_complete, b, r.c, plan->cus);
         auto hit = cache.find(key);
         if (hit != cache.end() && (!hit->second.wave || b.wave_ok || b.bip) &&
             (b.bip || hit->second.wave || b.max_block_per_cu[bt_index(hit->second.threads)] > 0)) {
@@ -783,10 +797,11 @@ ged_status ged_plan_tune(ged_plan *plan, ged_costs costs, int32_t *d_dist, int32
             if (st != GED_OK) break;
             continue;
         }
-        // candidates: the wavefront kernel and the workgroup kernel (256 and
-        // 512 threads), each at the occupancy limit and fractions of it; one
-        // candidate per distinct grid
+        // candidates: the wavefront kernel and the workgroup kernel (256, 512 and
+        // 1024 threads where they are kernels of their own), each at the occupancy
+        // limit and fractions of it; one candidate per distinct kernel and grid
         std::vector<Choice> cands;
+        std::vector<const void *> kernels;
         const int64_t nwork = (int64_t)b.h_sorted.size();
         for (int fam = 0; fam < 4; ++fam) {
             const bool wave = fam == 0;
@@ -794,7 +809,16 @@ ged_status ged_plan_tune(ged_plan *plan, ged_costs costs, int32_t *d_dist, int32
             if (wave && !b.wave_ok && !b.bip) continue;
             if (fam == 3 && b.max_block_per_cu[2] <= 0) continue;   // no 1024-thread instantiation
             const int threads = b.bip ? (fam == 0 ? 64 : 256) : bt_of(fam == 0 ? 0 : fam - 1);
-            const int lim = b.bip ? b.bip_max_per_cu[fam] : (wave ? b.max_wave_per_cu : b.max_block_per_cu[bt_index(threads)]);
+            int lim = b.bip ? b.bip_max_per_cu[fam] : (wave ? b.max_wave_per_cu : b.max_block_per_cu[bt_index(threads)]);
+            if (!b.bip && !wave) {
+                const gedk::BlockShape sh = shape_at(b, plan->K, threads);
+                const void *k = gedk::block_kernel(sh, r.c, (int)nwork, plan->cus);
+                if (std::find(kernels.begin(), kernels.end(), k) != kernels.end()) continue;
+                kernels.push_back(k);
+                if (b.both)
+                    lim = gedk::block_takes_mat(sh, r.c, nwork, plan->cus) ? b.mat_per_cu[bt_index(threads)]
+                                                                           : b.cand_per_cu[bt_index(threads)];
+            }
             int64_t last_grid = -1;
             for (int g = lim; g >= 1; g = g / 2) {
                 const int64_t grid = std::min<int64_t>(nwork, (int64_t)g * plan->cus);
