@@ -244,6 +244,12 @@ __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
     // (16 a thread instead: 512 pairs of 65..250, K = 64, 2,026 against 1,862 us)
     constexpr int MAXA = PARTS >= 4 ? 4 : 16 / PARTS;
     static_assert(W % 4 == 0 && KS <= T && 8 % UW == 0 && (2 * WU) % UW == 0, "shape");
+    // what the packed words below rest on
+    static_assert(16 * NT * (32 * WU / UW + 1) < 65536, "a wave's children: 16 bits of a threshold count");
+    static_assert(GED_MAX_K < 2048 && T * GED_MAX_K <= 1 << 21, "children below T in 11 bits, ties in the 21 above");
+    static_assert(32 * W < 1024, "counts over a row: 10 bits each");
+    static_assert(32 * WU < DELU && GED_MAX_K <= 1 << 21, "survivor record: slot above 10 bits of vertex");
+    static_assert(KS <= (KS > 256 ? 65536 : 256), "ancestor index");
 
     constexpr MatLds L = mat_lds(W, KS, NA, ND);
     extern __shared__ uint32_t s_dyn[];

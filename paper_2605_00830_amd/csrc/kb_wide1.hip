@@ -50,6 +50,8 @@ constexpr int MAXG = 2048;            // workgroups of a level
 constexpr int HC = 16;
 constexpr uint32_t NONE = 0xffffffffu;
 constexpr uint32_t DEL8 = 0xffu;
+static_assert(kWide1MaxN2 <= 32 && (uint32_t)kWide1MaxN2 < DEL8, "an image: a bit of a word, a byte");
+static_assert((int64_t)kWideMaxK << 6 <= (int64_t)1 << 32, "record");
 
 struct Level {
     uint32_t B;      // parents

@@ -56,6 +56,8 @@ constexpr int RS = 32 * CWD + 16; // LDS stride of a row word over a chunk's ver
 constexpr int MAXN = GED_MAX_VERTICES;
 constexpr uint32_t NONE = 0xffffffffu;
 constexpr int UBITS = 11;         // record: slot << UBITS | vertex (n2: the deletion)
+static_assert(MAXN < 1 << UBITS && (int64_t)kWideMaxK << UBITS <= (int64_t)1 << 32, "record");
+static_assert((int64_t)kWideMaxK * (MAXN + 1) < (int64_t)1 << 32, "children of a level: 32 bits");
 constexpr uint32_t kCommonMost = 1u << 16;   // beams whose oldest block is looked at
 
 struct Level {
