@@ -9,10 +9,11 @@
 
 namespace gedk {
 
-// Block-per-pair kernel family: any n <= 512, K <= GED_MAX_K; beam state and
-// the candidate matrix live in a per-block global workspace.  Workgroups of
-// 256 threads, or 512 for bins too small to fill the device (two waves per
-// SIMD on one pair instead of one).
+// Workgroup-per-pair kernels: any n <= 512, K <= GED_MAX_K.  A shape's BT is 256
+// threads, or 512 for bins too small to fill the device.  The candidate-matrix
+// kernel runs workgroups of that size (two waves per SIMD on one pair instead of
+// one); the matrix-core kernel picks its own by K, and takes BT for few or many
+// pairs.
 constexpr int kBlockThreads = 256;
 constexpr int kBlockThreadsWide = 512;
 constexpr int kBlockThreadsXL = 1024;   // unlabelled 8- and 16-word rows, one pair per CU

@@ -153,9 +153,9 @@ int default_threads(const ged_plan *p, const Bin &b) {
     // resident at once with one (the launch then lasts as long as its
     // slowest pair, which four waves shorten), else one
     if (b.bip) return (int64_t)b.h_sorted.size() <= (int64_t)b.bip_max_per_cu[0] * p->cus ? 256 : 64;
-    // the workgroup kernel: four waves per SIMD on one pair when the bin has
-    // at most one pair per CU (and the shape that instantiation), two when it
-    // cannot fill every CU twice, else one
+    // the workgroup kernel (candidate matrix): four waves per SIMD on one pair
+    // when the bin has at most one pair per CU (and the shape that
+    // instantiation), two when it cannot fill every CU twice, else one
     const int64_t n = (int64_t)b.h_sorted.size();
     if (n <= (int64_t)p->cus && b.max_block_per_cu[2] > 0) return gedk::kBlockThreadsXL;
     return n < 2 * (int64_t)p->cus ? gedk::kBlockThreadsWide : gedk::kBlockThreads;

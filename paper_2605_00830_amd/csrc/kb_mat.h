@@ -11,11 +11,15 @@
 // The 0/1 operands are fp4 (E2M1) matrices of the 16x16x128 MFMA: 32 bits of a
 // set become four registers of nibbles by (w >> j) & 0x11111111 (value 0.5,
 // lifted to 1 by the block scale), the same permutation of v on both sides.
-// FAST: eins, -edel (+ esub) and -esub are small multiples of one integer g
-// (fp4 holds 0, 1, 2, 3, 4, 6, 8, 12 times 0.5), so they ride in the slot
+// FAST: eins, -edel (+ esub) and -esub are each 0 to 3 times one power of two
+// (fp4 holds 0, 1, 2, 3, 4, 6, 8, 12 times 0.5, and the spread bits stand for
+// 0.5 to 2; the power of two is the block scale), so they ride in the slot
 // operand and one chain gives the whole child but for its base; otherwise the
-// counts come out separately and the PED is formed in int32.  All sums are
-// whole numbers below 2^24: the f32 accumulators are exact.  Used vertices are
+// counts come out separately and the PED is formed in int32: two chains and
+// more registers, 1.5 to 4 times as long (200 pairs of 130..250 vertices at
+// K = 64: 1,656 us FAST, 3,757 with edge costs of 15; 7,500 with the candidate
+// matrix).  All sums are whole numbers below 2^24: the f32 accumulators are
+// exact.  Used vertices are
 // struck out by one more MFMA, a unit matrix times Img at scale 2^24.
 //
 // A wave holds NT tiles of 16 slots (their operands in registers) and walks
@@ -61,10 +65,13 @@
 // 400 pairs of 65..128 at K = 1024 20,034 -> 6,379; 100 labelled pairs of
 // 300..500 at K = 64 131,104 -> 12,191; 200 labelled directed pairs of 130..250
 // at K = 80 41,755 -> 5,939.  A launch lasts as long as its largest pair.  A
-// level at 500 vertices, K = 256 is about 54 thousand cycles: 24.9 in the
-// scoring (the matrix instructions, 16 cycles each, and the vector ones do not
-// overlap on this part: the two add up), 5.5 in 1.4 threshold rounds, 4.8
-// marking survivors, 3.5 emitting, 7.1 in the update, 5.8 building Phi.
+// level of 500 vertices (p = 0.1) at K = 256 is 48.6 thousand cycles, 405
+// positions left: 23.8 in the scoring (7.4 of it waiting for the SIMD's other
+// wave), 4.9 in 1.13 threshold rounds, 4.4 marking survivors, 3.1 emitting, 6.8
+// in the update, 5.0 on the neighbours and Phi, 0.6 closing up.  The matrix
+// instructions (16 cycles each) and the vector ones hardly overlap on this part:
+// a stream of both takes 0.93 of the two alone added up.  Over a launch the
+// matrix pipes of the CUs at work are busy 15 % of the time, the vector pipes 54 %.
 #pragma once
 
 #include "ged_internal.h"
@@ -219,7 +226,8 @@ template <> struct AncOf<true> { using type = uint16_t; };
 // W: words of a row (directed: out-half, then in-half); a wave holds NT tiles
 // of 16 slots; SW waves split the slots, UW the target tiles.
 // MINW: waves per SIMD the registers are held to, four where that costs no
-// spills, so that two 512-thread workgroups fit a CU.
+// spills (two registers with directed label planes), so that two 512-thread
+// workgroups fit a CU.
 template <int W, int NT, int SW, int UW, bool LAB, bool DIR, bool FAST,
           int MINW = (FAST && NT == 1 && (W == 4 || (W == 8 && !LAB))) ? 4 : 2>
 __global__ __launch_bounds__(64 * SW * UW, MINW) void kb_mat_kernel(MatArgs a) {
