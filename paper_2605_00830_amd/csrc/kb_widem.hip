@@ -394,18 +394,6 @@ __global__ __launch_bounds__(WT) void wm_expand(Ctx c, int i, int chunks, int gr
     }
 }
 
-// PED of child u of slot p (u < n2, free), from the stored sets.
-__device__ __forceinline__ uint32_t child_ped(const Ctx &c, int i, uint32_t p, int u, uint32_t deg) {
-    uint32_t kept = 0u, in = 0u;
-    for (int k = 0; k < c.w2; ++k) {
-        const uint32_t row = c.a2[(size_t)u * c.w2 + k];
-        kept += (uint32_t)__popc(row & c.sets[(size_t)k * c.Kp + p]);
-        in += (uint32_t)__popc(row & c.img[i & 1][(size_t)k * c.Kp + p]);
-    }
-    return c.ped[i & 1][p] + (c.l2[u] != c.l1[i] ? (uint32_t)c.c.vsub : 0u) + (uint32_t)c.c.edel * (deg - kept) +
-           (uint32_t)c.c.eins * (in - kept);
-}
-
 // ------------------------------------------------------------------ mark
 // The level's threshold from its histogram, by every workgroup; *quota the
 // ties that survive.  Workgroup 0 also writes the next level's size and bounds.
@@ -788,10 +776,11 @@ __global__ __launch_bounds__(UT) void wm_update(Ctx c, int i, int groups) {
     }
 }
 
-// Edges of g2 inside slot s's Img, twice.
-__device__ __forceinline__ uint32_t inside2(const Ctx &c, int cur, uint32_t s) {
+// Edges of g2 inside slot s's Img, twice: the share of thread `part` of `parts`
+// (the image's words in turn).
+__device__ __forceinline__ uint32_t inside2(const Ctx &c, int cur, uint32_t s, int part, int parts) {
     uint32_t e = 0u;
-    for (int kw = 0; kw < c.w2; ++kw) {
+    for (int kw = part; kw < c.w2; kw += parts) {
         uint32_t m = c.img[cur][(size_t)kw * c.Kp + s];
         while (m) {
             const int u = 32 * kw + __builtin_ctz(m);
@@ -823,27 +812,33 @@ __device__ __forceinline__ void block_least(unsigned long long key, unsigned lon
 }
 
 // ------------------------------------------------------------------ complete-then-minimum
-// Last level with that option: every child's total (Sec. 4.4.1), four threads a
-// slot; the least (total, generation order) of each workgroup.
+// Last level with that option: every child's total (Sec. 4.4.1), CP threads a
+// slot; the least (total, generation order) of each workgroup.  CP: four keep the
+// slots' words coalesced (100 x 100 vertices, K = 200,000: 7.95 ms the search,
+// 8.41 with 16); with few slots they would leave most of the device idle (5 x 1000
+// at K = 2000: 1.48 ms the search so, 0.52 with 16 and without the second sum).
+constexpr uint32_t kCompleteFew = 1u << 14;   // slots that 16 threads each serve
+template <int CP>
 __global__ __launch_bounds__(WT) void wm_complete(Ctx c, int i) {
-    const int t = threadIdx.x, us = t / 4, part = t % 4, cur = i & 1;
-    const uint32_t B = sgpr(c.st[i].B), s = (uint32_t)blockIdx.x * GS + (uint32_t)us;
+    const int t = threadIdx.x, us = t / CP, part = t % CP, cur = i & 1;
+    const uint32_t B = sgpr(c.st[i].B), s = (uint32_t)blockIdx.x * (WT / CP) + (uint32_t)us;
     const uint32_t deg = sgpr(degree(c, i));
     unsigned long long key = ~0ull;
     uint32_t children = 0u;
     if (s < B) {
-        const uint32_t e0 = inside2(c, cur, s) / 2u, left = (uint32_t)c.n2 - c.nsub[cur][s];
-        for (int u = part; u <= c.n2; u += 4) {
-            uint32_t total;
+        const uint32_t e0 = parts_sum<CP>(inside2(c, cur, s, part, CP)) / 2u, left = (uint32_t)c.n2 - c.nsub[cur][s];
+        const uint32_t ped = c.ped[cur][s], eins = (uint32_t)c.c.eins, edel = (uint32_t)c.c.edel;
+        const int lab1 = c.l1[i];
+        for (int u = part; u <= c.n2; u += CP) {
+            uint32_t total = ped + deg * edel + (uint32_t)c.c.vins * left + eins * ((uint32_t)c.m2 - e0);   // (the deletion's)
             if (u < c.n2) {
                 if ((c.img[cur][(size_t)(u >> 5) * c.Kp + s] >> (u & 31)) & 1u) continue;
-                uint32_t add = 0u;
-                for (int k = 0; k < c.w2; ++k)
-                    add += (uint32_t)__popc(c.a2[(size_t)u * c.w2 + k] & c.img[cur][(size_t)k * c.Kp + s]);
-                total = child_ped(c, i, s, u, deg) + (uint32_t)c.c.vins * (left - 1u) + (uint32_t)c.c.eins * ((uint32_t)c.m2 - e0 - add);
+                // its edges into Img, inserted or kept now, are not inserted at the end
+                uint32_t kept = 0u;
+                for (int k = 0; k < c.w2; ++k) kept += (uint32_t)__popc(c.a2[(size_t)u * c.w2 + k] & c.sets[(size_t)k * c.Kp + s]);
+                total += (c.l2[u] != lab1 ? (uint32_t)c.c.vsub : 0u) - (uint32_t)c.c.vins - (edel + eins) * kept;
             } else {
-                total = c.ped[cur][s] + (uint32_t)c.c.vdel + deg * (uint32_t)c.c.edel + (uint32_t)c.c.vins * left +
-                        (uint32_t)c.c.eins * ((uint32_t)c.m2 - e0);
+                total += (uint32_t)c.c.vdel;
             }
             const unsigned long long k = ((unsigned long long)total << 32) | ((s << UBITS) | (uint32_t)u);
             key = k < key ? k : key;
@@ -880,17 +875,7 @@ __global__ __launch_bounds__(WT) void wm_pick(Ctx c, int i, int groups) {
 __global__ __launch_bounds__(WT) void wm_final_keys(Ctx c) {
     const int t = threadIdx.x, us = t / 4, part = t % 4, cur = c.n1 & 1;
     const uint32_t B = sgpr(c.st[c.n1].B), s = (uint32_t)blockIdx.x * GS + (uint32_t)us, at = min(s, B - 1u);
-    uint32_t e = 0u;   // the four threads split the rows of the image
-    for (int kw = part; kw < c.w2; kw += 4) {
-        uint32_t m = c.img[cur][(size_t)kw * c.Kp + at];
-        while (m) {
-            const int u = 32 * kw + __builtin_ctz(m);
-            m &= m - 1u;
-            for (int k = 0; k < c.w2; ++k)
-                e += (uint32_t)__popc(c.a2[(size_t)u * c.w2 + k] & c.img[cur][(size_t)k * c.Kp + at]);
-        }
-    }
-    e = quad_sum(e) / 2u;
+    const uint32_t e = quad_sum(inside2(c, cur, at, part, 4)) / 2u;
     unsigned long long key = ~0ull;
     if (s < B)
         key = ((unsigned long long)(c.ped[cur][s] + (uint32_t)c.c.vins * ((uint32_t)c.n2 - c.nsub[cur][s]) +
@@ -950,7 +935,7 @@ Layout layout(int n1, int w2, uint32_t Kp) {
     L.st = take((size_t)(n1 + 1) * sizeof(Level));
     L.prep = take(sizeof(Prep));
     L.ce = take(8);
-    L.best = take(groups * 8);
+    L.best = take(std::max<size_t>(groups, kCompleteFew / (WT / 16)) * 8);
     // (last: few levels touch them, and between the others they would put what
     // every level touches on further pages, 0.4 us of each of its launches)
     L.farc = take((size_t)FC * 4);
@@ -971,8 +956,10 @@ hipError_t levels(const Ctx &c, bool last_complete, hipStream_t stream) {
         const bool last = last_complete && i == c.n1 - 1;
         hipLaunchKernelGGL(wm_expand<W>, dim3(last ? g : g * chunks), dim3(WT), 0, stream, c, i, last ? 1 : chunks, groups, last ? 0 : 1);
         if (last) {
-            hipLaunchKernelGGL(wm_complete, dim3(g), dim3(WT), 0, stream, c, i);
-            hipLaunchKernelGGL(wm_pick, dim3(1), dim3(WT), 0, stream, c, i, g);
+            const int gc = bound <= kCompleteFew ? (int)((bound + WT / 16 - 1) / (WT / 16)) : g;
+            if (bound <= kCompleteFew) hipLaunchKernelGGL(wm_complete<16>, dim3(gc), dim3(WT), 0, stream, c, i);
+            else hipLaunchKernelGGL(wm_complete<WT / GS>, dim3(gc), dim3(WT), 0, stream, c, i);
+            hipLaunchKernelGGL(wm_pick, dim3(1), dim3(WT), 0, stream, c, i, gc);
             bound = 1;
             break;
         }
