@@ -24,7 +24,7 @@
 // so the beam stays in generation order.
 //
 // Two 20-vertex graphs at K = 1.2 million (MI355X): 2,325 us with the candidate
-// matrix of kb_wide.hip, 993 us so; a level of 1.2 million parents is 14 us of
+// matrix of kb_wide.hip, 975 us so; a level of 1.2 million parents is 14 us of
 // count (13 instructions a child), 12 us of emit and 23 us of update (it moves
 // about 75 MB).  Not kept: emit and update in one kernel, a workgroup writing
 // its own parents' survivors (53 us for the two: survivors gather under few
