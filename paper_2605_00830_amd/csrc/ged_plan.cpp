@@ -265,8 +265,8 @@ ged_status launch_bin(const ged_plan *p, const Bin &b, const RunCtx &r, bool per
         }
     } else if (!perpair) {
         const bool cand = b.both && !gedk::block_takes_mat(b.shape, r.c, nwork, p->cus);
-        GED_HIP(gedk::launch_block(b.shape, r.view, r.view, cand ? b.d_cand : b.d_work, nwork, b.d_queue, r.c, p->K, p->last_complete,
-                                   b.d_ws, b.ws_stride, r.o, b.grid, r.s));
+        GED_HIP(gedk::launch_block(b.shape, r.view, r.view, cand ? b.d_cand : b.d_work, nwork, b.d_queue, r.c, p->K,
+                                   p->last_complete, b.d_ws, b.ws_stride, r.o, b.grid, r.s));
     } else {
         for (int i = 0; i < nwork; ++i)
             GED_HIP(gedk::launch_block(b.shape, r.view, r.view, b.d_work + i, 1, b.d_queue + 1 + i, r.c, p->K,

@@ -130,7 +130,9 @@ struct ged_server {
     int PL = 0;
     int cus = 0;
     int wave_per_cu[kWaveBins] = {0, 0, 0};   // the wavefront families' kernels
-    int block_per_cu[2][5] = {};   // [256 | 512 threads][W = 1, 2, 4, 8, 16]
+    // [256 | 512 threads][W = 1, 2, 4, 8, 16]: resident workgroups of the shape's own kernel, and
+    // of the candidate-matrix kernel where a small target may take that instead (else 0)
+    int block_per_cu[2][5] = {}, cand_per_cu[2][5] = {};
     bool bip = false;              // bipartite method
     bool directed = false;         // directed database: rows [out | in], W doubled
     int bip_per_cu[kClasses] = {0, 0, 0, 0};   // its kernel, 1..4 columns per lane
@@ -342,7 +344,9 @@ hipError_t launch_batch(ged_server *s, Slab &b) {
             // workgroups per CU: a batch of large queries at full occupancy
             // would fill every SIMD's registers for tens of milliseconds and
             // keep the small and mid classes' waves off the device
-            const int per_cu = std::min(s->block_per_cu[wide][bin - kWaveBins], kBlockClassPerCu[b.cls]);
+            const int cand = shape[bin].mat_only ? 0 : s->cand_per_cu[wide][bin - kWaveBins];
+            const int per_cu =
+                std::min(cand > 0 ? cand : s->block_per_cu[wide][bin - kWaveBins], kBlockClassPerCu[b.cls]);
             grid[bin] = std::min({cnt, per_cu * s->cus, fit});
             if (grid[bin] <= 0) return hipErrorOutOfMemory;
         }
@@ -579,8 +583,12 @@ ged_status ged_server_create(ged_db *db, const ged_server_config *config, ged_se
             for (int wide = 0; wide < 2 && e == hipSuccess; ++wide) {
                 gedk::BlockShape sh = shape_for(s, W, max_n[cls], std::min(per_word * W, max_n[cls]),
                                                 wide ? gedk::kBlockThreadsWide : gedk::kBlockThreads);
-                e = gedk::block_max_resident(sh, &s->block_per_cu[wide][k]);
+                sh.nmax1 = std::min(max_n[cls], 128);   // (the rule for small targets is for short sources)
+                int mat = 0;
+                e = gedk::block_residents(sh, &mat, &s->cand_per_cu[wide][k]);
+                sh.nmax1 = max_n[cls];
                 sh.mat_only = true;   // what the least workspace has to hold
+                if (e == hipSuccess) e = gedk::block_max_resident(sh, &s->block_per_cu[wide][k]);
                 const int64_t grid =
                     std::min<int64_t>((int64_t)cfg.max_batch, (int64_t)s->block_per_cu[wide][k] * s->cus);
                 one_block = std::max(one_block, gedk::block_workspace_bytes(sh));
