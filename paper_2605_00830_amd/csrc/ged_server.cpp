@@ -130,9 +130,7 @@ struct ged_server {
     int PL = 0;
     int cus = 0;
     int wave_per_cu[kWaveBins] = {0, 0, 0};   // the wavefront families' kernels
-    // [256 | 512 threads][W = 1, 2, 4, 8, 16]: resident workgroups of the shape's own kernel, and
-    // of the candidate-matrix kernel where a small target may take that instead (else 0)
-    int block_per_cu[2][5] = {}, cand_per_cu[2][5] = {};
+    int block_per_cu[2][5] = {};   // [256 | 512 threads][W = 1, 2, 4, 8, 16]
     bool bip = false;              // bipartite method
     bool directed = false;         // directed database: rows [out | in], W doubled
     int bip_per_cu[kClasses] = {0, 0, 0, 0};   // its kernel, 1..4 columns per lane
@@ -188,6 +186,10 @@ gedk::BlockShape shape_for(const ged_server *s, int W, int nmax1, int nmax2, int
     sh.nmax2 = nmax2;
     sh.directed = s->directed ? 1 : 0;
     sh.K = s->cfg.K;
+    // (small targets on the candidate matrix gain next to nothing here, where
+    // batches are small and the host bounds them: 1500 queries of 10..30 vertices
+    // at K = 200, edge costs of 15, 3.2 ms without, 3.1 with it)
+    sh.mat_only = true;
     return sh;
 }
 
@@ -333,20 +335,13 @@ hipError_t launch_batch(ged_server *s, Slab &b) {
             const int wide = cnt < 2 * s->cus ? 1 : 0;
             shape[bin] = shape_for(s, 1 << (bin - kWaveBins), nmax1[bin], nmax2[bin],
                                    wide ? gedk::kBlockThreadsWide : gedk::kBlockThreads);
-            shape[bin].mat_only = gedk::block_takes_mat(shape[bin], s->c, cnt, s->cus);
             stride[bin] = gedk::block_workspace_bytes(shape[bin]);
-            if (stride[bin] > b.ws_bytes) {   // (a workspace holds one workgroup of every shape so)
-                shape[bin].mat_only = true;
-                stride[bin] = gedk::block_workspace_bytes(shape[bin]);
-            }
             const int fit = (int)std::min<size_t>(b.ws_bytes / stride[bin], (size_t)std::numeric_limits<int>::max());
             // the workgroup classes hold at most kBlockClassPerCu[class]
             // workgroups per CU: a batch of large queries at full occupancy
             // would fill every SIMD's registers for tens of milliseconds and
             // keep the small and mid classes' waves off the device
-            const int cand = shape[bin].mat_only ? 0 : s->cand_per_cu[wide][bin - kWaveBins];
-            const int per_cu =
-                std::min(cand > 0 ? cand : s->block_per_cu[wide][bin - kWaveBins], kBlockClassPerCu[b.cls]);
+            const int per_cu = std::min(s->block_per_cu[wide][bin - kWaveBins], kBlockClassPerCu[b.cls]);
             grid[bin] = std::min({cnt, per_cu * s->cus, fit});
             if (grid[bin] <= 0) return hipErrorOutOfMemory;
         }
@@ -581,14 +576,9 @@ ged_status ged_server_create(ged_db *db, const ged_server_config *config, ged_se
             const int W = 1 << k;
             if (W > (s->directed ? 2 : 1) && per_word * W / 2 >= max_n[cls]) break;   // W / 2 words already cover it
             for (int wide = 0; wide < 2 && e == hipSuccess; ++wide) {
-                gedk::BlockShape sh = shape_for(s, W, max_n[cls], std::min(per_word * W, max_n[cls]),
-                                                wide ? gedk::kBlockThreadsWide : gedk::kBlockThreads);
-                sh.nmax1 = std::min(max_n[cls], 128);   // (the rule for small targets is for short sources)
-                int mat = 0;
-                e = gedk::block_residents(sh, &mat, &s->cand_per_cu[wide][k]);
-                sh.nmax1 = max_n[cls];
-                sh.mat_only = true;   // what the least workspace has to hold
-                if (e == hipSuccess) e = gedk::block_max_resident(sh, &s->block_per_cu[wide][k]);
+                const gedk::BlockShape sh = shape_for(s, W, max_n[cls], std::min(per_word * W, max_n[cls]),
+                                                      wide ? gedk::kBlockThreadsWide : gedk::kBlockThreads);
+                e = gedk::block_max_resident(sh, &s->block_per_cu[wide][k]);
                 const int64_t grid =
                     std::min<int64_t>((int64_t)cfg.max_batch, (int64_t)s->block_per_cu[wide][k] * s->cus);
                 one_block = std::max(one_block, gedk::block_workspace_bytes(sh));
